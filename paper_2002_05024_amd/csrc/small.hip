@@ -11,46 +11,15 @@
 //    the paper cites), then a Householder Hessenberg reduction of the remaining
 //    spike and undeflated part.
 //
-// Four waves per workgroup.  In the QR iteration the chain of bulge steps is
-// latency-bound, so wave 0 runs it alone: each step updates only a near field
-// around the bulge (one pass: a mixed 4x3 block on lane 0, the columns to its
-// right and the rows above it on other lanes) and hands the next reflector's
-// input to every lane through a register broadcast.  Waves 1-3 meanwhile apply
-// the previous batch of FB reflectors to the far field (columns right of the
-// near field, rows above it, and the accumulated orthogonal factor).  Other
-// phases use all four waves with block barriers.
+// Four waves per workgroup.  In the QR iteration wave 0 works on the window alone
+// and waves 1 and 2 accumulate its reflectors into the orthogonal factor (see
+// there); other phases use all four waves with block barriers.
 #include "neig_dev.h"
 #include <climits>
 
 #define NT 256     // threads per workgroup
 #define LANES 64   // wavefront size
-#define FB 16      // reflectors per near-field batch
-
-// Optional section timers (compiled in with -DNEIG_PROF): shader clock cycles
-// accumulated by thread 0 into g_prof[0..7].
-#ifdef NEIG_PROF
-__shared__ long long g_prof[8];
-#define PROF_T(v) const long long v = clock64()
-#define PROF_ADD(slot, t0) do { if (threadIdx.x == 0) g_prof[slot] += clock64() - (t0); } while (0)
-#define PROF_CNT(slot, v) do { if (threadIdx.x == 0) g_prof[slot] += (v); } while (0)
-#else
-#define PROF_CNT(slot, v) do { } while (0)
-#define PROF_T(v)
-#define PROF_ADD(slot, t0) do { } while (0)
-#endif
-
-__device__ __forceinline__ double bcast_lane0(double v) {
-    const int lo = __builtin_amdgcn_readfirstlane(__double2loint(v));
-    const int hi = __builtin_amdgcn_readfirstlane(__double2hiint(v));
-    return __hiloint2double(hi, lo);
-}
-
-__device__ __forceinline__ void refl_apply3(double &a, double &b, double &c, double tau, double v1, double v2) {
-    const double t = tau * (a + v1 * b + v2 * c);
-    a -= t;
-    b -= t * v1;
-    c -= t * v2;
-}
+#define FB 15      // reflectors per batch handed to the accumulating waves
 
 // Block-wide max / sum (all NT threads call; result in every thread).
 __device__ __forceinline__ double block_reduce(double v, bool is_max) {
@@ -100,246 +69,511 @@ __device__ __forceinline__ void lds_standardise(double *T, int ldt, double *Q, i
     __syncthreads();
 }
 
-// Apply a batch of nb consecutive reflectors (positions k0..k0+nb-1) in order to
-// segments of the far field: columns c_lo..c_hi of T (rows k0..k0+nb+1), rows
-// 0..r_hi-1 of T (columns k0..k0+nb+1), and, if withq, every row of Q.  Work
-// items are spread over threads t0, t0+nth, ...  The coefficients are read into
-// registers once; segments of full length take a branch-free path.
-__device__ __forceinline__ void far_apply(double *T, int ldt, double *Q, int ldq, int m, int k0, int nb, int c_lo, int c_hi,
-                          int r_hi, bool withq, const double *rt, const double *r1, const double *r2, int t0, int nth) {
-    const int ncol = (c_hi >= c_lo) ? c_hi - c_lo + 1 : 0;
-    const int total = ncol + r_hi + (withq ? m : 0);
-    if (t0 >= total) return;
-    const int len = (k0 + nb + 2 <= m) ? nb + 2 : m - k0;
-    double ct[FB], c1[FB], c2[FB];
-#pragma unroll
-    for (int t = 0; t < FB; ++t) {
-        const bool on = t < nb;
-        ct[t] = on ? rt[t] : 0.0;
-        c1[t] = on ? r1[t] : 0.0;
-        c2[t] = on ? r2[t] : 0.0;
+// ---------------------------------------------------------------- double-shift QR in LDS
+//
+// Wave 0 runs the whole iteration on T by itself, without a block barrier: the
+// scan for negligible subdiagonals, the shifts, the bulge steps and the 2x2
+// standardisations.  The steps of a sweep are one dependent chain, so what
+// bounds them is the latency and the instruction count of one wave; T's entries
+// therefore pass through registers, not through LDS, on that chain:
+//
+//  * the 3x3 block under the reflector (the core), the subdiagonal entry below
+//    it and the generating vector are held by every lane, which all compute the
+//    same values: nothing on the chain crosses lanes;
+//  * lane c > k+2 holds rows k..k+2 of column c and lane r < k columns k..k+2 of
+//    row r, so one instruction sequence applies the reflector from the left to
+//    every column right of the core and from the right to every row above it.
+//    After a step each lane stores its first entry (final for this sweep), shifts,
+//    and loads the next one behind the next reflector's arithmetic; column k+3
+//    enters the core through readlane, row k leaves it by a select.
+//    T has at most 96 rows, so up to order 64 one vector per lane is enough and
+//    two above (SETS).
+//
+// The orthogonal factor does not feed back into T: waves 1 and 2 apply the
+// reflectors to Q's rows, in batches of FB that wave 0 publishes through a queue
+// in LDS.  Measured on MI355X on random 64-row windows (36 steps a sweep): 24 300
+// cycles a sweep, 45 900 when the entries passed through LDS and the other waves
+// updated the far part of T; the n = 20000 random reduction 1.61 -> 1.11 s, an
+// n = 40 block 1.03 -> 0.54 ms.
+//
+// Reflectors are kept as P = I + q u u^T, u = (x0 - beta, x1, x2),
+// q = 1 / (beta (x0 - beta)): the products u^T y then run beside the reciprocal
+// instead of after it.
+
+#define QR_SLOTS 4
+
+struct QrQueue {
+    double c[QR_SLOTS][FB][4];         // q, u0, u1, u2 of each reflector; or cs, sn of a rotation
+    int k0[QR_SLOTS], nb[QR_SLOTS];    // first position and count; 0: a rotation; -1: the end
+    int head;                          // entries published by wave 0
+    int tail[2];                       // entries applied by waves 1 and 2
+    int info, iters;
+    double dump[LANES];                // stores of lanes that have nothing to store
+};
+
+struct ReflU {
+    double beta, q, u0, u1, u2;
+};
+
+// The generating vector of a reflector, its squared length a, and the power of two
+// that it was scaled by when a left the range (u and q then belong to the scaled
+// vector; P is the same).  A zero vector becomes (1, 0, 0): a sign change.
+struct GenVec {
+    double x0, x1, x2, a, sc;
+};
+
+__device__ __forceinline__ GenVec gen_vec(double x0, double x1, double x2) {
+    GenVec g{x0, x1, x2, fma(x0, x0, fma(x1, x1, x2 * x2)), 1.0};
+    // a in about (1e-200, 1e200), by its exponent; the same in every lane
+    if (__builtin_expect(__ballot((unsigned)__double2hiint(g.a) - 0x16700000u < 0x53000000u) == 0ull, 0)) {
+        const double mx = fmax(fabs(x0), fmax(fabs(x1), fabs(x2)));
+        if (mx > 0.0 && mx < INFINITY) {
+            const int e = ilogb(mx);
+            g.x0 = ldexp(x0, -e); g.x1 = ldexp(x1, -e); g.x2 = ldexp(x2, -e);
+            g.sc = ldexp(1.0, e);
+        } else {
+            g.sc = x0 + x1 + x2;  // 0, or not finite
+            g.x0 = 1.0; g.x1 = 0.0; g.x2 = 0.0;
+        }
+        g.a = fma(g.x0, g.x0, fma(g.x1, g.x1, g.x2 * g.x2));
     }
-    const bool full = (len == FB + 2);
-    for (int it = t0; it < total; it += nth) {
-        double *base;
-        int stride;
-        if (it < ncol) {
-            base = &AT(T, ldt, k0, c_lo + it);
-            stride = 1;
-        } else if (it < ncol + r_hi) {
-            base = &AT(T, ldt, it - ncol, k0);
-            stride = ldt;
-        } else {
-            base = &AT(Q, ldq, it - ncol - r_hi, k0);
-            stride = ldq;
-        }
-        double x[FB + 2];
-        if (full) {
-#pragma unroll
-            for (int t = 0; t < FB + 2; ++t) x[t] = base[t * stride];
-#pragma unroll
-            for (int t = 0; t < FB; ++t) refl_apply3(x[t], x[t + 1], x[t + 2], ct[t], c1[t], c2[t]);
-#pragma unroll
-            for (int t = 0; t < FB + 2; ++t) base[t * stride] = x[t];
-        } else {
-#pragma unroll
-            for (int t = 0; t < FB + 2; ++t) x[t] = (t < len) ? base[t * stride] : 0.0;
-#pragma unroll
-            for (int t = 0; t < FB; ++t) refl_apply3(x[t], x[t + 1], x[t + 2], ct[t], c1[t], c2[t]);
-#pragma unroll
-            for (int t = 0; t < FB + 2; ++t)
-                if (t < len) base[t * stride] = x[t];
-        }
+    return g;
+}
+
+// Square root and reciprocal as in sqrt_normal and rcp_normal, with the
+// reciprocal started from the unrefined root, beside the refinement.
+__device__ __forceinline__ ReflU refl_u(const GenVec &x) {
+    ReflU r;
+    const double y = __builtin_amdgcn_rsq(x.a);
+    double g = x.a * y, h = 0.5 * y;
+    double z = __builtin_amdgcn_rcp(fma(fabs(x.x0), g, x.a));
+    const double e0 = fma(-g, h, 0.5);
+    g = fma(g, e0, g);
+    h = fma(h, e0, h);
+    g = fma(fma(-g, g, x.a), h, g);
+    const double beta = -copysign(g, x.x0);
+    r.u0 = x.x0 - beta;
+    const double den = beta * r.u0;  // -(a + |x0| sqrt(a))
+    z = -z;
+    z = fma(z, fma(-den, z, 1.0), z);
+    r.q = fma(z, fma(-den, z, 1.0), z);
+    r.u1 = x.x1;
+    r.u2 = x.x2;
+    r.beta = beta * x.sc;
+    return r;
+}
+
+// Orders this wave's LDS accesses across its lanes (the hardware keeps them in
+// program order; this keeps the compiler to it).
+__device__ __forceinline__ void wave_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+
+// A select of values (a conditional expression on struct members may become an
+// indexed load from scratch).
+__device__ __forceinline__ double pick(bool c, double a, double b) { return c ? a : b; }
+
+__device__ __forceinline__ double lane_value(double v, int lane) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                            __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+
+// Wave 0: the next queue slot, once the accumulating waves are done with it.
+__device__ __forceinline__ int qr_slot(QrQueue &q, int entry, int nacc) {
+    for (int w = 0; w < nacc; ++w)
+        while (__hip_atomic_load(&q.tail[w], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) + QR_SLOTS <= entry)
+            __builtin_amdgcn_s_sleep(1);
+    return entry & (QR_SLOTS - 1);
+}
+
+__device__ __forceinline__ void qr_publish(QrQueue &q, int entry, int k0, int nb) {
+    const int slot = entry & (QR_SLOTS - 1);
+    if ((threadIdx.x & (LANES - 1)) == 0) {
+        q.k0[slot] = k0;
+        q.nb[slot] = nb;
+        __hip_atomic_store(&q.head, entry + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
 }
 
-// One bulge step, reflector on rows/columns k..k+M3-1 (M3 = 3, or 2 at the last
-// step of a sweep), generated from (x0, x1, x2), recorded for the far field and
-// applied to the near field.  Every lane of wave 0 runs the same instructions on
-// a 3-vector of its own:
-//   lane c (0..31)   column k-1+c, rows k..k+M3-1: c = 0 receives (beta, 0, 0)
-//                    when k > l; columns k+M3..cnear take the left reflection;
-//   lane 32+t        row k0+t <= min(k+3, i), columns k..k+M3-1: rows k..k+M3-1
-//                    first take the left reflection of their entries (from the
-//                    column sums of the M3 x M3 diagonal block, which every
-//                    lane reads), then every row takes the right reflection.
-// The loads come first so that their latency hides behind the reflector's
-// dependent chain; only the stores are predicated.  The next generating vector
-// (column k, rows k+1..k+3) comes back from the row lanes through readlane.
-template <int M3>
-__device__ __forceinline__ void near_step(double *T, int ldt, int l, int i, int k, int k0, int cnear, double *rt,
-                                          double *r1, double *r2, double &x0, double &x1, double &x2) {
-    const int lane = threadIdx.x;
-    const int rmax = (k + 3 < i) ? k + 3 : i;
-    const bool isRow = lane >= 32;
-    const int col = k - 1 + lane;                 // column lanes
-    const int row = k0 + lane - 32;               // row lanes
-    const bool colOn = !isRow && lane > M3 && col <= cnear;
-    const bool betaOn = (lane == 0) && (k > l);
-    const bool rowOn = isRow && row <= rmax;
-    // the lane's 3-vector as a word offset and stride (idle lanes read word 0
-    // and store nothing); integer selects, no branches
-    const int off = colOn ? col * ldt + k : (rowOn ? k * ldt + row : 0);
-    const int vs = isRow ? ldt : 1;
-    double *vec = T + off;
-    double v[3];
+// Waves 1 and 2: apply the published entries to row `row` of Q (rows past m idle).
+__device__ __forceinline__ void qr_accumulate(QrQueue &q, int who, double *Q, int ldq, int m, int row) {
+    for (int entry = 0;; ++entry) {
+        while (__hip_atomic_load(&q.head, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) <= entry)
+            __builtin_amdgcn_s_sleep(1);
+        const int slot = entry & (QR_SLOTS - 1);
+        const int nb = __builtin_amdgcn_readfirstlane(q.nb[slot]);
+        if (nb < 0) break;
+        const int k0 = __builtin_amdgcn_readfirstlane(q.k0[slot]);
+        if (row < m) {
+            double *base = &AT(Q, ldq, row, k0);
+            if (nb == 0) {
+                const double cs = q.c[slot][0][0], sn = q.c[slot][0][1];
+                const double x = base[0], y = base[ldq];
+                base[0] = cs * x + sn * y;
+                base[ldq] = -sn * x + cs * y;
+            } else {
+                // reflectors past nb are zero (wave 0 clears a short batch's rest)
+                const int len = min(nb + 2, m - k0);
+                double x[FB + 2];
 #pragma unroll
-    for (int a = 0; a < M3; ++a) v[a] = vec[a * vs];
-    double blk[M3][M3];  // the diagonal block, same addresses for every lane
+                for (int t = 0; t < FB + 2; ++t) x[t] = (t < len) ? base[t * ldq] : 0.0;
 #pragma unroll
-    for (int a = 0; a < M3; ++a)
+                for (int t = 0; t < FB; ++t) {
+                    const double *c = q.c[slot][t];
+                    const double s = c[0] * fma(c[1], x[t], fma(c[2], x[t + 1], c[3] * x[t + 2]));
+                    x[t] = fma(s, c[1], x[t]);
+                    x[t + 1] = fma(s, c[2], x[t + 1]);
+                    x[t + 2] = fma(s, c[3], x[t + 2]);
+                }
 #pragma unroll
-        for (int b = 0; b < M3; ++b) blk[a][b] = AT(T, ldt, k + a, k + b);
-    Refl r = make_refl(x0, x1, (M3 == 3) ? x2 : 0.0);
-    const double w1 = r.v1, w2 = (M3 == 3) ? r.v2 : 0.0;
-    // left reflection of a row lane's entries in rows k..k+M3-1
-    const int q = row - k;
-    const double lw = (rowOn && q >= 0 && q < M3) ? r.tau * (q == 0 ? 1.0 : (q == 1 ? w1 : w2)) : 0.0;
-#pragma unroll
-    for (int b = 0; b < M3; ++b) {
-        double sc = blk[0][b] + w1 * blk[1][b];
-        if (M3 == 3) sc += w2 * blk[2][b];
-        v[b] -= lw * sc;
-    }
-    // the step's own reflection: left for column lanes, right for row lanes
-    double s = v[0] + w1 * v[1];
-    if (M3 == 3) s += w2 * v[2];
-    s *= r.tau;
-    v[0] -= s;
-    v[1] -= s * w1;
-    if (M3 == 3) v[2] -= s * w2;
-    if (colOn || rowOn) {
-#pragma unroll
-        for (int a = 0; a < M3; ++a) vec[a * vs] = v[a];
-    }
-    if (lane == 0) {
-        if (betaOn) {
-            AT(T, ldt, k, k - 1) = r.beta;
-            AT(T, ldt, k + 1, k - 1) = 0.0;
-            if (M3 == 3) AT(T, ldt, k + 2, k - 1) = 0.0;
+                for (int t = 0; t < FB + 2; ++t)
+                    if (t < len) base[t * ldq] = x[t];
+            }
         }
-        rt[k - k0] = r.tau;
-        r1[k - k0] = w1;
-        r2[k - k0] = w2;
+        if ((threadIdx.x & (LANES - 1)) == 0)
+            __hip_atomic_store(&q.tail[who], entry + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
-    const int lb = 32 + (k + 1 - k0);
-    x0 = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v[0]), lb),
-                          __builtin_amdgcn_readlane(__double2loint(v[0]), lb));
-    x1 = (k + 2 <= rmax) ? __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v[0]), lb + 1),
-                                            __builtin_amdgcn_readlane(__double2loint(v[0]), lb + 1))
-                         : 0.0;
-    x2 = (k + 3 <= rmax) ? __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v[0]), lb + 2),
-                                            __builtin_amdgcn_readlane(__double2loint(v[0]), lb + 2))
-                         : 0.0;
 }
 
-// Wave 0: bulge steps k0..k1-1 of the double-shift sweep on rows/cols l..i with
-// only the near field updated (columns up to cnear, rows from k0).  (x0, x1, x2)
-// carries the generating vector of the next step between calls.  Reflectors with
-// tau = 0 are exact no-ops, so no step is special-cased.
-__device__ __forceinline__ void near_steps(double *T, int ldt, int l, int i, int k0, int k1, int cnear, double tr, double det,
-                           double *rt, double *r1, double *r2, double &x0, double &x1, double &x2) {
-    if (k0 == l) {  // the sweep's first step: the bulge from the shift polynomial
-        const double h00 = AT(T, ldt, l, l), h01 = AT(T, ldt, l, l + 1);
-        const double h10 = AT(T, ldt, l + 1, l), h11 = AT(T, ldt, l + 1, l + 1);
-        const double h21 = AT(T, ldt, l + 2, l + 1);
-        double sc = fmax(fmax(fabs(h00), fabs(h01)), fmax(fmax(fabs(h10), fabs(h11)), fabs(h21)));
+// One implicit double-shift sweep (wave 0) on the active rows l..i (i - l >= 2) of
+// the m x m LDS matrix T, over all of T's rows and columns; entry counts the
+// queue's entries.  ldt > m: row m of T is never read as data, and takes the
+// stores of lanes that hold nothing.
+template <int SETS>
+__device__ __forceinline__ void qr_sweep(double *T, int ldt, int m, int l, int i, double tr, double det, QrQueue &q,
+                                         int nacc, int &entry) {
+    const int lane = threadIdx.x & (LANES - 1);
+    double C[3][3], x0, x1, x2;
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int b = 0; b < 3; ++b) C[a][b] = AT(T, ldt, l + a, l + b);
+    // per lane: its 3-vector, the address of the first entry and the stride.
+    // Lanes k+1 and k+2 (rows and columns of the core) go on storing as columns:
+    // what they write, T(k, k+1) and T(k, k+2), is stored again by lane k as a row.
+    double v[SETS][3];
+    int at[SETS], st[SETS];
+#pragma unroll
+    for (int s = 0; s < SETS; ++s) {
+        const int idx = lane + LANES * s;
+        at[s] = idx < l ? idx + l * ldt : (idx < m ? idx * ldt + l : m + min(idx - m, m - 1) * ldt);
+        st[s] = idx < l ? ldt : (idx < m ? 1 : 0);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) v[s][a] = T[at[s] + a * st[s]];
+    }
+    double h = AT(T, ldt, l + 3, l + 2);  // used only when l + 3 <= i
+    {  // the bulge from the shift polynomial
+        double sc = fmax(fmax(fabs(C[0][0]), fabs(C[0][1])), fmax(fmax(fabs(C[1][0]), fabs(C[1][1])), fabs(C[2][1])));
         sc = fmax(sc, fmax(fabs(tr), sqrt(fabs(det))));
         if (sc == 0.0) sc = 1.0;
         const double rs = 1.0 / sc;
-        const double a = h00 * rs, b = h01 * rs, c = h10 * rs, d = h11 * rs, e = h21 * rs;
+        const double a = C[0][0] * rs, b = C[0][1] * rs, c = C[1][0] * rs, d = C[1][1] * rs, e = C[2][1] * rs;
         const double t = tr * rs, dt = det * rs * rs;
         x0 = a * a + b * c - t * a + dt;
         x1 = c * (a + d - t);
         x2 = c * e;
     }
-    // three-row reflectors up to k = i - 2, the sweep's last (two-row) one at k = i - 1
-    const int k3 = (k1 < i - 1) ? k1 : i - 1;
-    int k = k0;
-    for (; k < k3; ++k) near_step<3>(T, ldt, l, i, k, k0, cnear, rt, r1, r2, x0, x1, x2);
-    if (k < k1) near_step<2>(T, ldt, l, i, k, k0, cnear, rt, r1, r2, x0, x1, x2);
-}
-
-// The far-field update of a sweep's last batch of reflectors (columns right of
-// its near field, the rows above it, all of Q) may be left pending: every entry
-// it writes is strictly above the diagonal, so the deflation scan does not read
-// them, and the next sweep's waves 1-3 apply it while wave 0 chases the first
-// batch, when that batch's near field lies left of its columns.  Otherwise (and
-// before a 2x2 standardisation, shift inputs it may touch, or the end) it is
-// applied by all threads at once.
-struct FarPending {
-    int k0, nb, cnear, buf;  // the batch (k0 < 0: none) and its reflector buffer
-};
-
-__device__ __forceinline__ void far_flush(double *T, int ldt, double *Q, int ldq, int m, FarPending &pf,
-                                          double (*rq)[3][FB]) {
-    if (pf.k0 < 0) return;
-    PROF_T(pf0);
-    far_apply(T, ldt, Q, ldq, m, pf.k0, pf.nb, pf.cnear + 1, m - 1, pf.k0, true, rq[pf.buf][0], rq[pf.buf][1],
-              rq[pf.buf][2], threadIdx.x, NT);
-    __syncthreads();
-    PROF_ADD(2, pf0);
-    pf.k0 = -1;
-}
-
-// One implicit double-shift step (all NT threads call) on the active rows l..i
-// of the m x m LDS matrix T; updates span all of T and Q's columns, except the
-// far field of the last batch, which is left pending in pf.
-__device__ __forceinline__ void lds_francis(double *T, int ldt, double *Q, int ldq, int m, int l, int i, double tr, double det,
-                                            FarPending &pf, double (*rq)[3][FB]) {
-    const int tid = threadIdx.x, wave = tid / LANES;
-    PROF_CNT(4, i - l);
-    {
-        const int k1 = (l + FB < i) ? l + FB : i;
-        const int cnear = (k1 + 1 < m - 1) ? k1 + 1 : m - 1;
-        if (pf.k0 >= 0 && cnear >= pf.k0) far_flush(T, ldt, Q, ldq, m, pf, rq);
-    }
-    double x0 = 0.0, x1 = 0.0, x2 = 0.0;
-    bool carried = pf.k0 >= 0;  // the previous sweep's last batch, for waves 1-3
-    int pk0 = pf.k0, pnb = pf.nb, pcnear = pf.cnear, pb = pf.buf, cb = carried ? pf.buf ^ 1 : 0;
-    for (int k0 = l; k0 <= i - 1; k0 += FB) {
-        const int k1 = (k0 + FB < i) ? k0 + FB : i;
-        const int cnear = (k1 + 1 < m - 1) ? k1 + 1 : m - 1;
-        if (wave == 0) {
-            PROF_T(pa);
-            if (pk0 >= 0 && !carried && cnear > pcnear)  // previous batch on the columns entering the near field
-                far_apply(T, ldt, Q, ldq, m, pk0, pnb, pcnear + 1, cnear, 0, false, rq[pb][0], rq[pb][1], rq[pb][2],
-                          tid, LANES);
-            near_steps(T, ldt, l, i, k0, k1, cnear, tr, det, rq[cb][0], rq[cb][1], rq[cb][2], x0, x1, x2);
-            PROF_ADD(0, pa);
-        } else if (pk0 >= 0) {
-            // a carried batch's near field is complete: all of its far field here
-            const int c_lo = carried ? pcnear + 1 : cnear + 1;
-            far_apply(T, ldt, Q, ldq, m, pk0, pnb, c_lo, m - 1, pk0, true, rq[pb][0], rq[pb][1], rq[pb][2],
-                      tid - LANES, NT - LANES);
+    int k0 = l;
+    int slot = qr_slot(q, entry, nacc);
+    // lanes 0..3 store a reflector's q, u0, u1, u2 into the queue, lane 4 its beta
+    double *qc = lane < 4 ? &q.c[slot][0][lane] : (lane == 4 ? T + (l + 1) + l * ldt : &q.dump[lane]);
+    const int qinc = lane < 4 ? 4 : (lane == 4 ? ldt + 1 : 0);
+    auto publish = [&](int nb) {
+        if (lane >= nb && lane < FB)
+            for (int a = 0; a < 4; ++a) q.c[slot][lane][a] = 0.0;
+        qr_publish(q, entry, k0, nb);
+        ++entry;
+        k0 += nb;
+        slot = qr_slot(q, entry, nacc);
+        if (lane < 4) qc = &q.c[slot][0][lane];
+    };
+    auto record = [&](const ReflU &r, bool first) __attribute__((always_inline)) {
+        const double w = pick(lane == 0, r.q, pick(lane == 1, r.u0, pick(lane == 2, r.u1,
+                                                                    pick(lane == 3, r.u2, r.beta))));
+        if (first) {  // no column left of the active block
+            *(lane == 4 ? &q.dump[lane] : qc) = w;
+            qc += lane < 4 ? 4 : 0;
+        } else {
+            *qc = w;
+            qc += qinc;
         }
-        PROF_T(pw);
-        __syncthreads();
-        PROF_ADD(1, pw);
-        carried = false;
-        pk0 = k0;
-        pnb = k1 - k0;
-        pcnear = cnear;
-        pb = cb;
-        cb ^= 1;
+    };
+    // The lanes' part of step k (reflector r, J the row k of the core): behind the
+    // chain of the next step, in the same block of instructions.  more: column
+    // k + 3 enters the core next.
+    auto lanes_step = [&](const ReflU &r, const double (&J)[3], int k, bool more) __attribute__((always_inline)) {
+        // row k joins the lanes
+#pragma unroll
+        for (int s = 0; s < SETS; ++s) {
+            const bool mine = lane + LANES * s == k;
+#pragma unroll
+            for (int b = 0; b < 3; ++b) v[s][b] = mine ? J[b] : v[s][b];
+            at[s] = mine ? k + k * ldt : at[s];
+            st[s] = mine ? ldt : st[s];
+        }
+        // left on the columns, right on the rows
+#pragma unroll
+        for (int s = 0; s < SETS; ++s) {
+            const double t = r.q * fma(r.u0, v[s][0], fma(r.u1, v[s][1], r.u2 * v[s][2]));
+            T[at[s]] = fma(t, r.u0, v[s][0]);
+            v[s][0] = fma(t, r.u1, v[s][1]);
+            v[s][1] = fma(t, r.u2, v[s][2]);
+        }
+        wave_fence();
+        if (more) {
+            const int c = k + 3;
+            double p1 = lane_value(v[0][0], c & (LANES - 1)), p2 = lane_value(v[0][1], c & (LANES - 1));
+            if (SETS == 2) {
+                const double p3 = lane_value(v[SETS - 1][0], c & (LANES - 1));
+                const double p4 = lane_value(v[SETS - 1][1], c & (LANES - 1));
+                p1 = c >= LANES ? p3 : p1;
+                p2 = c >= LANES ? p4 : p2;
+            }
+            C[0][2] = p1;
+            C[1][2] = p2;
+#pragma unroll
+            for (int s = 0; s < SETS; ++s) v[s][2] = T[at[s] + 3 * st[s]];
+        }
+#pragma unroll
+        for (int s = 0; s < SETS; ++s) at[s] += st[s];
+    };
+    // The core's part of step k; more: row and column k + 3 belong to the active block.
+    ReflU r;
+    double J[3];
+    auto core_step = [&](const GenVec &x, int k, bool first, bool more) __attribute__((always_inline)) {
+        r = refl_u(x);
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {  // left
+            const double t = r.q * fma(r.u0, C[0][b], fma(r.u1, C[1][b], r.u2 * C[2][b]));
+            J[b] = fma(t, r.u0, C[0][b]);
+            C[1][b] = fma(t, r.u1, C[1][b]);
+            C[2][b] = fma(t, r.u2, C[2][b]);
+        }
+#pragma unroll
+        for (int a = 1; a < 3; ++a) {  // right, on rows k+1, k+2: they move up
+            const double t = r.q * fma(r.u0, C[a][0], fma(r.u1, C[a][1], r.u2 * C[a][2]));
+            (a == 1 ? x0 : x1) = fma(t, r.u0, C[a][0]);
+            C[a - 1][0] = fma(t, r.u1, C[a][1]);
+            C[a - 1][1] = fma(t, r.u2, C[a][2]);
+        }
+        if (more) {  // right, on row k+3
+            const double t = r.q * (r.u2 * h);
+            x2 = t * r.u0;
+            C[2][0] = t * r.u1;
+            C[2][1] = fma(t, r.u2, h);
+            const int c = k + 3;
+            C[2][2] = AT(T, ldt, c, c);
+            h = AT(T, ldt, c + 1, c);  // row m, unused, when c = m - 1
+        }
+        record(r, first);
+    };
+    int k = l;
+    core_step(gen_vec(x0, x1, x2), k, true, k < i - 2);
+    ++k;
+    // One step: the range check of its reflector, then the lanes' part of the step
+    // before it between the dependent operations of this one's reflector.  The
+    // scheduling barriers keep that order (left alone, the compiler issues the
+    // reflector's chain in one piece, with a wait at every operation).
+    auto step = [&](bool more) __attribute__((always_inline)) {
+        const GenVec x = gen_vec(x0, x1, x2);
+        const double q = r.q, u0 = r.u0, u1 = r.u1, u2 = r.u2;  // step k - 1
+        double vv[SETS][3], t[SETS];
+        const double y = __builtin_amdgcn_rsq(x.a);
+#pragma unroll
+        for (int s = 0; s < SETS; ++s) {  // row k - 1 joins the lanes
+            const bool mine = lane + LANES * s == k - 1;
+#pragma unroll
+            for (int b = 0; b < 3; ++b) vv[s][b] = pick(mine, J[b], v[s][b]);
+            at[s] = mine ? (k - 1) + (k - 1) * ldt : at[s];
+            st[s] = mine ? ldt : st[s];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        double g = x.a * y, h2 = 0.5 * y;
+#pragma unroll
+        for (int s = 0; s < SETS; ++s) t[s] = u2 * vv[s][2];
+        __builtin_amdgcn_sched_barrier(0);
+        double z = -__builtin_amdgcn_rcp(fma(fabs(x.x0), g, x.a));
+        const double e0 = fma(-g, h2, 0.5);
+#pragma unroll
+        for (int s = 0; s < SETS; ++s) t[s] = fma(u1, vv[s][1], t[s]);
+        __builtin_amdgcn_sched_barrier(0);
+        g = fma(g, e0, g);
+        h2 = fma(h2, e0, h2);
+#pragma unroll
+        for (int s = 0; s < SETS; ++s) t[s] = fma(u0, vv[s][0], t[s]);
+        __builtin_amdgcn_sched_barrier(0);
+        const double d = fma(-g, g, x.a);
+#pragma unroll
+        for (int s = 0; s < SETS; ++s) t[s] *= q;
+        __builtin_amdgcn_sched_barrier(0);
+        g = fma(d, h2, g);
+#pragma unroll
+        for (int s = 0; s < SETS; ++s) {
+            T[at[s]] = fma(t[s], u0, vv[s][0]);
+            v[s][0] = fma(t[s], u1, vv[s][1]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        const double beta = -copysign(g, x.x0);
+        const double w0 = x.x0 - beta, w1 = x.x1, w2 = x.x2;
+#pragma unroll
+        for (int s = 0; s < SETS; ++s) v[s][1] = fma(t[s], u2, vv[s][2]);
+        __builtin_amdgcn_sched_barrier(0);
+        const double den = beta * w0;
+        {  // column k + 2 enters the core
+            const int c = (k + 2) & (LANES - 1);
+            double p1 = lane_value(v[0][0], c), p2 = lane_value(v[0][1], c);
+            if (SETS == 2) {
+                const double p3 = lane_value(v[SETS - 1][0], c), p4 = lane_value(v[SETS - 1][1], c);
+                p1 = k + 2 >= LANES ? p3 : p1;
+                p2 = k + 2 >= LANES ? p4 : p2;
+            }
+            C[0][2] = p1;
+            C[1][2] = p2;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        const double e1 = fma(-den, z, 1.0);
+        double dot[3];
+#pragma unroll
+        for (int b = 0; b < 3; ++b) dot[b] = w2 * C[2][b];
+        __builtin_amdgcn_sched_barrier(0);
+        z = fma(z, e1, z);
+#pragma unroll
+        for (int b = 0; b < 3; ++b) dot[b] = fma(w1, C[1][b], dot[b]);
+        __builtin_amdgcn_sched_barrier(0);
+        const double e2 = fma(-den, z, 1.0);
+#pragma unroll
+        for (int b = 0; b < 3; ++b) dot[b] = fma(w0, C[0][b], dot[b]);
+        const double w2h = w2 * h;
+        __builtin_amdgcn_sched_barrier(0);
+        const double p = fma(z, e2, z);
+        wave_fence();
+        if (SETS == 1) v[0][2] = T[at[0] + 3 * st[0]];
+        else
+#pragma unroll
+            for (int s = 0; s < SETS; ++s) v[s][2] = T[at[s] + 3 * st[s]];
+#pragma unroll
+        for (int s = 0; s < SETS; ++s) at[s] += st[s];
+        double C22 = 0.0, hn = 0.0;
+        if (more) {
+            C22 = AT(T, ldt, k + 3, k + 3);
+            hn = AT(T, ldt, k + 4, k + 3);  // row m, unused, when k + 3 = m - 1
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int b = 0; b < 3; ++b) dot[b] *= p;
+        const double th = p * w2h;
+        double R1[3], R2[3];
+#pragma unroll
+        for (int b = 2; b >= 0; --b) {  // left, on the core
+            R1[b] = fma(dot[b], w1, C[1][b]);
+            R2[b] = fma(dot[b], w2, C[2][b]);
+        }
+        // right, on its rows 1 and 2
+        double s1 = w2 * R1[2], s2 = w2 * R2[2];
+        s1 = fma(w1, R1[1], s1);
+        s2 = fma(w1, R2[1], s2);
+        s1 = p * fma(w0, R1[0], s1);
+        s2 = p * fma(w0, R2[0], s2);
+        x0 = fma(s1, w0, R1[0]);
+        x1 = fma(s2, w0, R2[0]);
+        if (more) x2 = th * w0;
+#pragma unroll
+        for (int b = 0; b < 3; ++b) J[b] = fma(dot[b], w0, C[0][b]);
+        C[0][0] = fma(s1, w1, R1[1]);
+        C[0][1] = fma(s1, w2, R1[2]);
+        C[1][0] = fma(s2, w1, R2[1]);
+        C[1][1] = fma(s2, w2, R2[2]);
+        if (more) {  // row k + 3
+            C[2][0] = th * w1;
+            C[2][1] = fma(th, w2, h);
+            C[2][2] = C22;
+            h = hn;
+        }
+        r.q = p; r.u0 = w0; r.u1 = w1; r.u2 = w2; r.beta = beta * x.sc;
+        record(r, false);
+        ++k;
+    };
+    while (k < i - 2) {
+        const int ke = min(i - 2, k0 + FB);
+        while (k + 3 <= ke) {  // by three, so that the shifts cost no moves
+            step(true);
+            step(true);
+            step(true);
+        }
+        while (k < ke) step(true);
+        if (k - k0 == FB) publish(FB);
     }
-    pf.k0 = pk0;
-    pf.nb = pnb;
-    pf.cnear = pcnear;
-    pf.buf = pb;
+    if (k == i - 2) step(false);
+    if (k - k0 == FB) publish(FB);
+    lanes_step(r, J, k - 1, false);
+    // the last, two-row reflector at k = i - 1, on core rows 0, 1 and columns 0, 1
+    {
+        const ReflU e = refl_u(gen_vec(x0, x1, 0.0));
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            const double t = e.q * fma(e.u0, C[0][b], e.u1 * C[1][b]);
+            C[0][b] = fma(t, e.u0, C[0][b]);
+            C[1][b] = fma(t, e.u1, C[1][b]);
+        }
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+            const double t = e.q * fma(e.u0, C[a][0], e.u1 * C[a][1]);
+            C[a][0] = fma(t, e.u0, C[a][0]);
+            C[a][1] = fma(t, e.u1, C[a][1]);
+        }
+#pragma unroll
+        for (int s = 0; s < SETS; ++s) {
+            const int idx = lane + LANES * s;
+            const double t = e.q * fma(e.u0, v[s][0], e.u1 * v[s][1]);
+            if ((unsigned)(idx - k) > 1u && idx < m) {
+                T[at[s]] = fma(t, e.u0, v[s][0]);
+                T[at[s] + st[s]] = fma(t, e.u1, v[s][1]);
+            }
+        }
+        record(e, false);
+        if (lane == 0) {
+            AT(T, ldt, k, k) = C[0][0]; AT(T, ldt, k, k + 1) = C[0][1];
+            AT(T, ldt, k + 1, k) = C[1][0]; AT(T, ldt, k + 1, k + 1) = C[1][1];
+        }
+    }
+    publish(k - k0 + 1);
+    wave_fence();
 }
 
-// Double-shift QR iteration on the m x m LDS matrix T (upper Hessenberg) with Q
-// accumulated.  Returns 0, or i+1 when rows/cols 0..i did not converge within
-// maxit iterations.  *iters receives the iteration count.
-__device__ __forceinline__ int lds_small_qr(double *T, int ldt, double *Q, int ldq, int m, double hnorm, double smlnum, int maxit,
-                            int *iters) {
-    __shared__ double rq[2][3][FB];
+// Wave 0: standard form of the 2x2 block at (j, j) of T.
+__device__ __forceinline__ void qr_standardise(double *T, int ldt, int m, int j, QrQueue &q, int nacc, int &entry) {
     const int lane = threadIdx.x & (LANES - 1);
-    FarPending pf{-1, 0, 0, 0};
-    int i = m - 1, its = 0, total = 0;
+    const Std2 o = std2x2(AT(T, ldt, j, j), AT(T, ldt, j, j + 1), AT(T, ldt, j + 1, j), AT(T, ldt, j + 1, j + 1));
+    if (!(o.cs == 1.0 && o.sn == 0.0)) {
+        for (int idx = lane; idx < m; idx += LANES) {
+            if (idx == j || idx == j + 1) continue;
+            double *p = (idx < j) ? &AT(T, ldt, idx, j) : &AT(T, ldt, j, idx);
+            const int s = (idx < j) ? ldt : 1;
+            const double x = p[0], y = p[s];
+            p[0] = o.cs * x + o.sn * y;
+            p[s] = -o.sn * x + o.cs * y;
+        }
+        const int slot = qr_slot(q, entry, nacc);
+        if (lane == 0) {
+            q.c[slot][0][0] = o.cs;
+            q.c[slot][0][1] = o.sn;
+        }
+        qr_publish(q, entry, j, 0);
+        ++entry;
+    }
+    if (lane == 0) {
+        AT(T, ldt, j, j) = o.a; AT(T, ldt, j, j + 1) = o.b;
+        AT(T, ldt, j + 1, j) = o.c; AT(T, ldt, j + 1, j + 1) = o.d;
+    }
+    wave_fence();
+}
+
+// Wave 0: the whole iteration.  Returns 0, or i+1 when rows/cols 0..i did not
+// converge within maxit iterations.
+template <int SETS>
+__device__ __forceinline__ int qr_iterate(double *T, int ldt, int m, double hnorm, double smlnum, int maxit, QrQueue &q,
+                                          int nacc, int &entry, int *iters) {
+    const int lane = threadIdx.x & (LANES - 1);
+    int i = m - 1, its = 0, total = 0, info = 0;
     while (i >= 0) {
-        PROF_T(pe);
         int l = 0;
         for (int base = i; base >= 1; base -= LANES) {
             const int k = base - lane;
@@ -352,33 +586,26 @@ __device__ __forceinline__ int lds_small_qr(double *T, int ldt, double *Q, int l
                 break;
             }
         }
-        __syncthreads();
-        if (l > 0 && threadIdx.x == 0) AT(T, ldt, l, l - 1) = 0.0;
-        __syncthreads();
-        PROF_ADD(3, pe);
+        wave_fence();
+        if (l > 0 && lane == 0) AT(T, ldt, l, l - 1) = 0.0;
+        wave_fence();
         if (l == i) {
             --i;
             its = 0;
             continue;
         }
         if (l == i - 1) {
-            far_flush(T, ldt, Q, ldq, m, pf, rq);
-            lds_standardise(T, ldt, Q, ldq, m, i - 1);
+            qr_standardise(T, ldt, m, i - 1, q, nacc, entry);
             i -= 2;
             its = 0;
             continue;
         }
         if (total >= maxit) {
-            far_flush(T, ldt, Q, ldq, m, pf, rq);
-            *iters = total;
-            return i + 1;
+            info = i + 1;
+            break;
         }
         ++total;
         ++its;
-        // the shift inputs: T(i-1, i) is the only one off the two diagonals
-        if (pf.k0 >= 0 && ((i - 1 < pf.k0 && i >= pf.k0 && i <= pf.k0 + pf.nb + 1) ||
-                           (i - 1 >= pf.k0 && i - 1 <= pf.k0 + pf.nb + 1 && i > pf.cnear)))
-            far_flush(T, ldt, Q, ldq, m, pf, rq);
         double tr, det;
         if (its == 10 || its == 20) {
             const double s = fabs(AT(T, ldt, i, i - 1)) + fabs(AT(T, ldt, i - 1, i - 2));
@@ -391,12 +618,46 @@ __device__ __forceinline__ int lds_small_qr(double *T, int ldt, double *Q, int l
             tr = a + d;
             det = a * d - b * c;
         }
-        __syncthreads();  // every wave has read the shift inputs before wave 0 writes
-        lds_francis(T, ldt, Q, ldq, m, l, i, tr, det, pf, rq);
+        qr_sweep<SETS>(T, ldt, m, l, i, tr, det, q, nacc, entry);
     }
-    far_flush(T, ldt, Q, ldq, m, pf, rq);
     *iters = total;
-    return 0;
+    return info;
+}
+
+// Double-shift QR iteration on the m x m LDS matrix T (upper Hessenberg, m <= 96)
+// with Q accumulated; all NT threads call, after a barrier.  Returns 0, or i+1
+// when rows/cols 0..i did not converge within maxit iterations.  *iters receives
+// the iteration count.
+__device__ __forceinline__ int lds_small_qr(double *T, int ldt, double *Q, int ldq, int m, double hnorm, double smlnum,
+                                            int maxit, int *iters) {
+    static_assert(NEIG_SMALL_MAX <= 2 * LANES, "two vectors per lane");
+    __shared__ QrQueue q;
+    const int lane = threadIdx.x & (LANES - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / LANES);
+    if (threadIdx.x == 0) {
+        q.head = 0;
+        q.tail[0] = q.tail[1] = 0;
+    }
+    __syncthreads();
+    const int nacc = (m + LANES - 1) / LANES;  // accumulating waves
+    if (wave == 0) {
+        int entry = 0, its = 0;
+        const int info = (m <= LANES) ? qr_iterate<1>(T, ldt, m, hnorm, smlnum, maxit, q, nacc, entry, &its)
+                                      : qr_iterate<2>(T, ldt, m, hnorm, smlnum, maxit, q, nacc, entry, &its);
+        qr_slot(q, entry, nacc);
+        qr_publish(q, entry, 0, -1);
+        if (lane == 0) {
+            q.info = info;
+            q.iters = its;
+        }
+    } else if (wave <= nacc) {
+        qr_accumulate(q, wave - 1, Q, ldq, m, lane + LANES * (wave - 1));
+    }
+    __syncthreads();
+    *iters = q.iters;
+    const int info = q.info;
+    __syncthreads();
+    return info;
 }
 
 // Load the m x m diagonal block of H at (off, off) into T (zeros below the
@@ -427,11 +688,6 @@ k_small_qr(double *H, int ldh, int off, int m, double hnorm, double smlnum, int 
     const int ld = m + 1;
     double *T = lds;
     double *Q = lds + (size_t)m * ld;
-#ifdef NEIG_PROF
-    if (threadIdx.x < 8) g_prof[threadIdx.x] = 0;
-    __syncthreads();
-    const long long p0 = clock64();
-#endif
     lds_load_block(H, ldh, off, m, T, ld, Q, ld);
     int iters = 0;
     const int info = lds_small_qr(T, ld, Q, ld, m, hnorm, smlnum, maxit, &iters);
@@ -440,10 +696,6 @@ k_small_qr(double *H, int ldh, int off, int m, double hnorm, double smlnum, int 
     if (threadIdx.x == 0) {
         status[0] = info;
         status[1] = iters;
-#ifdef NEIG_PROF
-        g_prof[7] = clock64() - p0;
-        for (int t = 0; t < 8; ++t) ((long long *)(status + 16))[t] = g_prof[t];
-#endif
     }
 }
 
@@ -773,7 +1025,6 @@ __device__ __forceinline__ bool swap_transform(const double (&B)[P + Q][P + Q], 
         if constexpr (P == 2 && Q == 2) {
             double Xc[4];
             if (sylv22_closed(B, Xc) && swap_from_x<2, 2>(B, Xc, bnorm, Qm, Bn)) return true;
-            PROF_CNT(7, 1);  // the closed form was rejected: 4 x 4 solve
         } else {
             double Xc[2];
             if (sylv12_closed<P, Q>(B, Xc) && swap_from_x<P, Q>(B, Xc, bnorm, Qm, Bn)) return true;
@@ -862,10 +1113,7 @@ __device__ __forceinline__ bool lds_swap(double *T, int ldt, double *V, int ldv,
     if (p == 1 && q == 1) return lds_swap_pq<1, 1>(T, ldt, V, ldv, nw, st);
     if (p == 1 && q == 2) return lds_swap_pq<1, 2>(T, ldt, V, ldv, nw, st);
     if (p == 2 && q == 1) return lds_swap_pq<2, 1>(T, ldt, V, ldv, nw, st);
-    PROF_T(p22);
     const bool ok = lds_swap_pq<2, 2>(T, ldt, V, ldv, nw, st);
-    PROF_CNT(5, 1);
-    PROF_ADD(6, p22);
     return ok;
 }
 
