@@ -158,14 +158,42 @@ __device__ __forceinline__ bool negligible_sub(double sub, double dkm1, double d
     return fabs(sub) <= fmax(smlnum, NEIG_EPS * s);
 }
 
+// One step of a wavefront reduction: the value that the given cross-lane move brings
+// to a lane, or `none` where it brings nothing.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_move(double v, double none) {
+    const int lo = __builtin_amdgcn_update_dpp(__double2loint(none), __double2loint(v), CTRL, ROWS, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(__double2hiint(none), __double2hiint(v), CTRL, ROWS, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
+
+__device__ __forceinline__ double last_lane(double v) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 63),
+                            __builtin_amdgcn_readlane(__double2loint(v), 63));
+}
+
+// Sum and maximum over a wavefront, in every lane; all 64 lanes call.  Shifts
+// within the rows of 16 lanes, then the rows' last lanes to the rows after them:
+// register moves, about 25 cycles a step, where a shuffle goes through the LDS
+// unit (about 130).
 __device__ __forceinline__ double wave_sum(double v) {
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
+    v += dpp_move<0x111, 0xf>(v, 0.0);
+    v += dpp_move<0x112, 0xf>(v, 0.0);
+    v += dpp_move<0x114, 0xf>(v, 0.0);
+    v += dpp_move<0x118, 0xf>(v, 0.0);
+    v += dpp_move<0x142, 0xa>(v, 0.0);
+    v += dpp_move<0x143, 0xc>(v, 0.0);
+    return last_lane(v);
 }
 
 __device__ __forceinline__ double wave_max(double v) {
-    for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
-    return v;
+    v = fmax(v, dpp_move<0x111, 0xf>(v, v));
+    v = fmax(v, dpp_move<0x112, 0xf>(v, v));
+    v = fmax(v, dpp_move<0x114, 0xf>(v, v));
+    v = fmax(v, dpp_move<0x118, 0xf>(v, v));
+    v = fmax(v, dpp_move<0x142, 0xa>(v, v));
+    v = fmax(v, dpp_move<0x143, 0xc>(v, v));
+    return last_lane(v);
 }
 
 // Eigenvalues of a 2x2 block (any form): returns real parts and |imag|.

@@ -111,6 +111,30 @@ struct QrQueue {
     double dump[LANES];                // stores of lanes that have nothing to store
 };
 
+#define SWAP_PAIRS 32    // pairs of one round (more wait for the next one)
+#define SWAP_ROWS 384    // largest window
+
+// One round of block swaps (see there).
+struct SwapState {
+    double q[SWAP_PAIRS][16];        // the transforms, N x N at i + N j
+    int total, cnt[4], rejected;
+    int list[4][SWAP_PAIRS];         // per type: slots
+    int st[SWAP_PAIRS], n[SWAP_PAIRS];  // per slot: first row (-1: rejected) and rows
+    unsigned char head[SWAP_ROWS + 1];  // 1: a block starts at this row
+    unsigned char mover[SWAP_ROWS];     // 1: a block that moves up starts at this row
+};
+
+// The scratch in LDS that the phases of a window kernel use in turn.
+union WinScratch {
+    QrQueue qr;
+    SwapState sw;
+};
+
+__device__ __forceinline__ WinScratch &win_scratch() {
+    __shared__ WinScratch s;
+    return s;
+}
+
 struct ReflU {
     double beta, q, u0, u1, u2;
 };
@@ -631,7 +655,7 @@ __device__ __forceinline__ int qr_iterate(double *T, int ldt, int m, double hnor
 __device__ __forceinline__ int lds_small_qr(double *T, int ldt, double *Q, int ldq, int m, double hnorm, double smlnum,
                                             int maxit, int *iters) {
     static_assert(NEIG_SMALL_MAX <= 2 * LANES, "two vectors per lane");
-    __shared__ QrQueue q;
+    QrQueue &q = win_scratch().qr;
     const int lane = threadIdx.x & (LANES - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / LANES);
     if (threadIdx.x == 0) {
@@ -1052,125 +1076,234 @@ __device__ __forceinline__ bool swap_transform(const double (&B)[P + Q][P + Q], 
     }
 }
 
-// Swap the adjacent diagonal blocks of T at st (sizes P then Q) in place, with
-// the transformation applied to whole rows/columns of the nw x nw window and to V.
+// ---------------------------------------------------------------- rounds of swaps
+//
+// Blocks that move up ("movers") are swapped past the blocks above them in
+// rounds: in one round every mover whose upper neighbour is not a mover swaps
+// with it.  The pairs of a round are disjoint, so their transforms act on
+// disjoint rows and columns and commute; the order of the swaps along each path
+// is that of moving the blocks one after another.  A round computes all
+// transforms first, one per lane, wave (p - 1) * 2 + (q - 1) those of a p x p
+// block above a q x q one (a transform is 700 dependent instructions for two 2x2
+// blocks: it costs a round once, not once per swap), then applies them from the
+// left to the rows right of each pair, then from the right to the columns above
+// it and to V.  What bounds a round is the 2x2-2x2 transform and the four
+// barriers (about 7000 cycles).  Measured on MI355X: random 64-row deflation
+// windows (555 swaps each) 1.80 -> 0.73 million cycles, the random n = 20000
+// reduction 1.11 -> 0.83 s; 96-row reordering windows 1183 -> 418 us.
+
+// Block starts of the quasi-triangular window T, no movers.  All NT threads
+// call, after a barrier; ends with one.
+__device__ __forceinline__ void swap_begin(SwapState &w, const double *T, int ld, int nw) {
+    for (int r = threadIdx.x; r <= nw; r += NT) {
+        w.head[r] = r == 0 || r == nw || AT(T, ld, r, r - 1) == 0.0;
+        if (r < nw) w.mover[r] = 0;
+    }
+    if (threadIdx.x == 0) {
+        w.total = 0;
+        w.rejected = 0;
+        for (int t = 0; t < 4; ++t) w.cnt[t] = 0;
+    }
+    __syncthreads();
+}
+
+// The transforms of one type's pairs, one per lane.
 template <int P, int Q>
-__device__ __forceinline__ bool lds_swap_pq(double *T, int ldt, double *V, int ldv, int nw, int st) {
+__device__ __forceinline__ void swap_transforms(SwapState &w, int type, double *T, int ld) {
     constexpr int N = P + Q;
+    const int lane = threadIdx.x & (LANES - 1);
+    if (lane >= w.cnt[type]) return;
+    const int slot = w.list[type][lane];
+    const int st = w.st[slot];
     double B[N][N], Qm[N][N], Bn[N][N];
 #pragma unroll
     for (int i = 0; i < N; ++i)
 #pragma unroll
-        for (int j = 0; j < N; ++j) B[i][j] = AT(T, ldt, st + i, st + j);
-    const bool ok = swap_transform<P, Q>(B, Qm, Bn);
-    __syncthreads();
-    if (!ok) return false;
-    const int ncol = nw - (st + N);
-    const int total = ncol + st + nw;
-    for (int it = threadIdx.x; it < total; it += NT) {
-        if (it < ncol) {  // rows st..st+N-1 right of the pair: new = Qm^T old
-            const int j = st + N + it;
+        for (int j = 0; j < N; ++j) B[i][j] = AT(T, ld, st + i, st + j);
+    if (!swap_transform<P, Q>(B, Qm, Bn)) {
+        w.st[slot] = -1;
+        w.rejected = 1;
+        return;
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            w.q[slot][i + N * j] = Qm[i][j];
+            AT(T, ld, st + i, st + j) = Bn[i][j];
+        }
+    w.mover[st + P] = 0;
+    w.head[st + P] = P == Q;
+    w.head[st + Q] = 1;
+    w.mover[st] = 1;
+}
+
+// Apply a pair's transform: rows st.. right of the pair (left), or columns st..
+// of the rows above it and of V (right); one wave.
+template <int N>
+__device__ __forceinline__ void swap_apply(double *T, double *V, int ld, int nw, int st, const double *q, bool left) {
+    const int lane = threadIdx.x & (LANES - 1);
+    double Qm[N][N];
+#pragma unroll
+    for (int j = 0; j < N; ++j)
+#pragma unroll
+        for (int i = 0; i < N; ++i) Qm[i][j] = q[i + N * j];
+    if (left) {
+        for (int c = st + N + lane; c < nw; c += LANES) {
             double o[N];
 #pragma unroll
-            for (int i = 0; i < N; ++i) o[i] = AT(T, ldt, st + i, j);
+            for (int i = 0; i < N; ++i) o[i] = AT(T, ld, st + i, c);
 #pragma unroll
             for (int i = 0; i < N; ++i) {
                 double d = 0.0;
 #pragma unroll
                 for (int k = 0; k < N; ++k) d += Qm[k][i] * o[k];
-                AT(T, ldt, st + i, j) = d;
+                AT(T, ld, st + i, c) = d;
             }
-        } else {  // columns st..st+N-1 of the rows above (T) and of V: new = old Qm
-            const int i = it - ncol;
-            double *M = (i < st) ? T : V;
-            const int ld = (i < st) ? ldt : ldv;
-            const int row = (i < st) ? i : i - st;
+        }
+    } else {
+        for (int it = lane; it < st + nw; it += LANES) {
+            double *p = (it < st) ? &AT(T, ld, it, st) : &AT(V, ld, it - st, st);
             double o[N];
 #pragma unroll
-            for (int k = 0; k < N; ++k) o[k] = AT(M, ld, row, st + k);
+            for (int k = 0; k < N; ++k) o[k] = p[(size_t)k * ld];
 #pragma unroll
             for (int j = 0; j < N; ++j) {
                 double d = 0.0;
 #pragma unroll
                 for (int k = 0; k < N; ++k) d += o[k] * Qm[k][j];
-                AT(M, ld, row, st + j) = d;
+                p[(size_t)j * ld] = d;
             }
         }
     }
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int i = 0; i < N; ++i)
-#pragma unroll
-            for (int j = 0; j < N; ++j) AT(T, ldt, st + i, st + j) = Bn[i][j];
+}
+
+__device__ __forceinline__ void swap_apply_all(SwapState &w, double *T, double *V, int ld, int nw, int pairs,
+                                               bool left) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / LANES);
+    for (int s = wave; s < pairs; s += NT / LANES) {
+        const int st = __builtin_amdgcn_readfirstlane(w.st[s]), n = __builtin_amdgcn_readfirstlane(w.n[s]);
+        if (st < 0) continue;
+        if (n == 2) swap_apply<2>(T, V, ld, nw, st, w.q[s], left);
+        else if (n == 3) swap_apply<3>(T, V, ld, nw, st, w.q[s], left);
+        else swap_apply<4>(T, V, ld, nw, st, w.q[s], left);
+    }
+}
+
+// One round on rows top..kend-1: every mover swaps with the block above it if
+// that is not a mover.  Returns the number of pairs (0: nothing can move); all
+// NT threads call, after a barrier; ends with one.
+__device__ __forceinline__ int swap_round(SwapState &w, double *T, double *V, int ld, int nw, int top, int kend) {
+    for (int r = top + 1 + (int)threadIdx.x; r < kend; r += NT) {
+        if (!w.mover[r]) continue;
+        const int a = w.head[r - 1] ? r - 1 : r - 2;
+        if (a < top || w.mover[a]) continue;
+        const int slot = atomicAdd(&w.total, 1);
+        if (slot >= SWAP_PAIRS) continue;
+        const int p = r - a, q = w.head[r + 1] ? 1 : 2, type = (p - 1) * 2 + (q - 1);
+        w.st[slot] = a;
+        w.n[slot] = p + q;
+        w.list[type][atomicAdd(&w.cnt[type], 1)] = slot;
     }
     __syncthreads();
-    // the 2x2 blocks of Bn are similar to the old ones but not in standard form;
-    // aed_core standardises the deflated ones once, after all swaps
-    return true;
+    const int pairs = min(w.total, SWAP_PAIRS);
+    if (pairs == 0) return 0;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / LANES);
+    if (wave == 0) swap_transforms<1, 1>(w, 0, T, ld);
+    else if (wave == 1) swap_transforms<1, 2>(w, 1, T, ld);
+    else if (wave == 2) swap_transforms<2, 1>(w, 2, T, ld);
+    else swap_transforms<2, 2>(w, 3, T, ld);
+    __syncthreads();
+    swap_apply_all(w, T, V, ld, nw, pairs, true);
+    if (threadIdx.x == 0) {
+        w.total = 0;
+        for (int t = 0; t < 4; ++t) w.cnt[t] = 0;
+    }
+    __syncthreads();
+    swap_apply_all(w, T, V, ld, nw, pairs, false);
+    __syncthreads();
+    // the 2x2 blocks of a swapped pair are similar to the old ones but not in
+    // standard form; the caller standardises them once, after all swaps
+    return pairs;
 }
 
-__device__ __forceinline__ bool lds_swap(double *T, int ldt, double *V, int ldv, int nw, int st, int p, int q) {
-    if (p == 1 && q == 1) return lds_swap_pq<1, 1>(T, ldt, V, ldv, nw, st);
-    if (p == 1 && q == 2) return lds_swap_pq<1, 2>(T, ldt, V, ldv, nw, st);
-    if (p == 2 && q == 1) return lds_swap_pq<2, 1>(T, ldt, V, ldv, nw, st);
-    const bool ok = lds_swap_pq<2, 2>(T, ldt, V, ldv, nw, st);
-    return ok;
+// ---------------------------------------------------------------- Householder helpers
+
+// Sum over the four lanes of a quad; the same in all four.
+__device__ __forceinline__ double quad_sum(double v) {
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), 0xB1, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), 0xB1, 0xf, 0xf, true);
+    v += __hiloint2double(hi, lo);
+    const int lo2 = __builtin_amdgcn_mov_dpp(__double2loint(v), 0x4E, 0xf, 0xf, true);
+    const int hi2 = __builtin_amdgcn_mov_dpp(__double2hiint(v), 0x4E, 0xf, 0xf, true);
+    return v + __hiloint2double(hi2, lo2);
 }
 
-// ---------------------------------------------------------------- Householder helpers (vector in LDS)
-
-// Turn x[0..len-1] (LDS) into a Householder vector in place: on return
-// x[0] = 1, x[1..] = v, *tau and *beta set.  All NT threads call.
-__device__ __forceinline__ void lds_house(double *x, int len, double *tau, double *beta) {
-    const double alpha = x[0];
+// The Householder vector of g(0..len-1), computed by every wave on its own (no
+// barrier) and written to x with x[0] = 1 by the first; tau = 0 when the tail is
+// zero.  sc scales the vector into range.
+template <class G>
+__device__ __forceinline__ void win_house(G g, double *x, int len, double *tau, double *beta) {
+    const int lane = threadIdx.x & (LANES - 1);
+    const double alpha = g(0);
     double mx = 0.0;
-    for (int t = 1 + (int)threadIdx.x; t < len; t += NT) mx = fmax(mx, fabs(x[t]));
-    mx = block_reduce(mx, true);
+    for (int t = 1 + lane; t < len; t += LANES) mx = fmax(mx, fabs(g(t)));
+    mx = wave_max(mx);
     if (mx == 0.0) {
         *tau = 0.0;
         *beta = alpha;
-        __syncthreads();
-        if (threadIdx.x == 0) x[0] = 1.0;
-        __syncthreads();
         return;
     }
-    const double sc = fmax(mx, fabs(alpha));
+    const double sc = fmax(mx, fabs(alpha)), rs = 1.0 / sc;
     double ss = 0.0;
-    for (int t = 1 + (int)threadIdx.x; t < len; t += NT) ss += (x[t] / sc) * (x[t] / sc);
-    ss = block_reduce(ss, false) + (alpha / sc) * (alpha / sc);
+    for (int t = 1 + lane; t < len; t += LANES) ss += (g(t) * rs) * (g(t) * rs);
+    ss = wave_sum(ss) + (alpha * rs) * (alpha * rs);
     const double nrm = sc * sqrt(ss);
     const double b = alpha >= 0.0 ? -nrm : nrm;
     *tau = (b - alpha) / b;
     *beta = b;
     const double inv = 1.0 / (alpha - b);
-    __syncthreads();
-    for (int t = 1 + (int)threadIdx.x; t < len; t += NT) x[t] *= inv;
-    if (threadIdx.x == 0) x[0] = 1.0;
-    __syncthreads();
+    if (threadIdx.x < LANES)
+        for (int t = lane; t < len; t += LANES) x[t] = (t == 0) ? 1.0 : g(t) * inv;
 }
 
+// Householder vectors are applied by quads: the four lanes of a quad share a
+// column (left) or a row (right) and take every fourth element of the vector, so
+// a window's 64 columns or rows go through in one pass of quarter length
+// (64-row windows, 39 columns reduced: 0.56 -> 0.28 million cycles; one thread per
+// column or row and block-wide reductions before).
+
 // rows r0..r0+len-1 of M, columns c0..c1, from the left by I - tau v v^T
-__device__ __forceinline__ void lds_refl_left(double *M, int ld, int r0, int len, int c0, int c1, double tau, const double *v) {
-    for (int j = c0 + (int)threadIdx.x; j <= c1; j += NT) {
+__device__ __forceinline__ void win_refl_left(double *M, int ld, int r0, int len, int c0, int c1, double tau,
+                                              const double *v) {
+    const int part = threadIdx.x & 3;
+    for (int j0 = c0; j0 <= c1; j0 += NT / 4) {
+        const int j = j0 + (int)threadIdx.x / 4;
+        const bool on = j <= c1;
+        double *p = &AT(M, ld, r0, on ? j : c1);
         double d = 0.0;
-        for (int t = 0; t < len; ++t) d += v[t] * AT(M, ld, r0 + t, j);
-        d *= tau;
-        for (int t = 0; t < len; ++t) AT(M, ld, r0 + t, j) -= d * v[t];
+        for (int t = part; t < len; t += 4) d += v[t] * p[t];
+        d = tau * quad_sum(d);
+        if (on)
+            for (int t = part; t < len; t += 4) p[t] -= d * v[t];
     }
 }
 
-// columns c0..c0+len-1 of M (rows r0..r1) and of M2 (rows 0..r2-1), from the right
-__device__ __forceinline__ void lds_refl_right2(double *M, int ld, int r0, int r1, double *M2, int ld2, int r2, int c0, int len,
-                                double tau, const double *v) {
-    const int n1 = (r1 >= r0) ? r1 - r0 + 1 : 0;
-    for (int it = threadIdx.x; it < n1 + r2; it += NT) {
-        double *A = (it < n1) ? M : M2;
-        const int lda = (it < n1) ? ld : ld2;
-        const int i = (it < n1) ? r0 + it : it - n1;
+// columns c0..c0+len-1 of M (rows 0..r1) and of M2 (rows 0..r2-1), from the right
+__device__ __forceinline__ void win_refl_right2(double *M, int ld, int r1, double *M2, int r2, int c0, int len,
+                                                double tau, const double *v) {
+    const int part = threadIdx.x & 3;
+    const int total = r1 + 1 + r2;
+    for (int i0 = 0; i0 < total; i0 += NT / 4) {
+        const int it = i0 + (int)threadIdx.x / 4;
+        const bool on = it < total;
+        const int i = on ? it : total - 1;
+        double *p = (i <= r1) ? &AT(M, ld, i, c0) : &AT(M2, ld, i - r1 - 1, c0);
         double d = 0.0;
-        for (int t = 0; t < len; ++t) d += AT(A, lda, i, c0 + t) * v[t];
-        d *= tau;
-        for (int t = 0; t < len; ++t) AT(A, lda, i, c0 + t) -= d * v[t];
+        for (int t = part; t < len; t += 4) d += p[(size_t)t * ld] * v[t];
+        d = tau * quad_sum(d);
+        if (on)
+            for (int t = part; t < len; t += 4) p[(size_t)t * ld] -= d * v[t];
     }
 }
 
@@ -1230,35 +1363,35 @@ __device__ __forceinline__ void aed_deflate(double *T, double *V, int ld, double
     o.nswap = 0;
     o.late = 0;
     o.swapfail = 0;
-    int top = o.infqr, kend = nw;
+    SwapState &w = win_scratch().sw;
+    swap_begin(w, T, ld, nw);
+    const int top = o.infqr;
+    int kend = nw;
+    bool moving = false;
     while (kend > top) {
-        const int bs = (kend - 2 >= top && AT(T, ld, kend - 1, kend - 2) != 0.0) ? 2 : 1;
-        const int j = kend - bs;
-        const bool defl = aed_block_deflates(T, V, ld, s, j, bs, hnorm, smlnum, criterion);
-        __syncthreads();  // all threads have read the test inputs before any swap writes
-        if (defl) {
-            if (top > o.infqr) o.late += bs;
-            kend -= bs;
-            continue;
-        }
-        int pos = j;
-        bool ok = true;
-        while (pos > top) {
-            const int ba = (pos - 2 >= top && AT(T, ld, pos - 1, pos - 2) != 0.0) ? 2 : 1;
-            const int st = pos - ba;
-            if (!lds_swap(T, ld, V, ld, nw, st, ba, bs)) {
-                ok = false;
-                break;
+        // test the bottom block unless it is on its way up; what lies below a
+        // block that failed has already passed it
+        const int j = w.head[kend - 1] ? kend - 1 : kend - 2;
+        if (!w.mover[j]) {
+            const int bs = kend - j;
+            if (aed_block_deflates(T, V, ld, s, j, bs, hnorm, smlnum, criterion)) {
+                if (moving) o.late += bs;
+                kend = j;
+                continue;
             }
-            ++o.nswap;
-            pos = st;
+            moving = true;
+            __syncthreads();  // every thread has read the marks
+            if (tid == 0) w.mover[j] = 1;
+            __syncthreads();
         }
-        if (!ok) {
+        const int pairs = swap_round(w, T, V, ld, nw, top, kend);
+        if (pairs == 0) break;  // all movers have arrived
+        if (w.rejected) {
+            // the rest counts as undeflatable
             o.swapfail = 1;
-            top = kend;
             break;
         }
-        top += bs;
+        o.nswap += pairs;
     }
     o.nd = nw - kend;
     // standard form for the deflated 2x2 blocks (swaps leave them in any form);
@@ -1303,34 +1436,33 @@ __device__ __forceinline__ void aed_deflate(double *T, double *V, int ld, double
 
     if (kend > 0 && s != 0.0) {
         __syncthreads();
-        for (int t = tid; t < kend; t += NT) x[t] = s * AT(V, ld, 0, t);
-        __syncthreads();
         if (kend > 1) {
             double tau, beta;
-            lds_house(x, kend, &tau, &beta);
+            win_house([&](int t) { return s * AT(V, ld, 0, t); }, x, kend, &tau, &beta);
             o.spike0 = beta;
+            __syncthreads();
             if (tau != 0.0) {
-                lds_refl_left(T, ld, 0, kend, 0, nw - 1, tau, x);
+                win_refl_left(T, ld, 0, kend, 0, nw - 1, tau, x);
                 __syncthreads();
-                lds_refl_right2(T, ld, 0, kend - 1, V, ld, nw, 0, kend, tau, x);
+                win_refl_right2(T, ld, kend - 1, V, nw, 0, kend, tau, x);
                 __syncthreads();
             }
             // Householder Hessenberg reduction of the undeflated leading block
             for (int cc = 0; cc + 2 < kend; ++cc) {
                 const int len = kend - cc - 1;
-                for (int t = tid; t < len; t += NT) x[t] = AT(T, ld, cc + 1 + t, cc);
-                __syncthreads();
+                double *col = &AT(T, ld, cc + 1, cc);
                 double tau2, beta2;
-                lds_house(x, len, &tau2, &beta2);
-                if (tau2 == 0.0) continue;
-                for (int t = tid; t < len; t += NT) AT(T, ld, cc + 1 + t, cc) = (t == 0) ? beta2 : 0.0;
-                lds_refl_left(T, ld, cc + 1, len, cc + 1, nw - 1, tau2, x);
+                win_house([&](int t) { return col[t]; }, x, len, &tau2, &beta2);
                 __syncthreads();
-                lds_refl_right2(T, ld, 0, kend - 1, V, ld, nw, cc + 1, len, tau2, x);
+                if (tau2 == 0.0) continue;
+                for (int t = tid; t < len; t += NT) col[t] = (t == 0) ? beta2 : 0.0;
+                win_refl_left(T, ld, cc + 1, len, cc + 1, nw - 1, tau2, x);
+                __syncthreads();
+                win_refl_right2(T, ld, kend - 1, V, nw, cc + 1, len, tau2, x);
                 __syncthreads();
             }
         } else {
-            o.spike0 = x[0];
+            o.spike0 = s * AT(V, ld, 0, 0);
         }
     }
     __syncthreads();
@@ -1459,27 +1591,16 @@ k_reorder_window(double *S, int lds_, const ReorderWin *wins, double *Vt_all, in
     const int ld = w + 1;
     double *T = lds, *V = lds + (size_t)w * ld;
     lds_load_block(S, lds_, off, w, T, ld, V, ld);
-    int placed = 0, fail = 0, j = 0;
-    while (j < w) {
-        const int bs = (j + 1 < w && AT(T, ld, j + 1, j) != 0.0) ? 2 : 1;
-        if (!f.sel[j]) {
-            j += bs;
-            continue;
-        }
-        int pos = j;
-        while (pos > placed) {
-            const int ba = (pos - 2 >= placed && AT(T, ld, pos - 1, pos - 2) != 0.0) ? 2 : 1;
-            const int st = pos - ba;
-            if (!lds_swap(T, ld, V, ld, w, st, ba, bs)) {
-                fail = 1;
-                break;
-            }
-            pos = st;
-        }
-        if (fail) break;
-        placed += bs;
-        j += bs;
+    // every selected block moves up past the unselected ones above it
+    SwapState &sw = win_scratch().sw;
+    swap_begin(sw, T, ld, w);
+    for (int j = threadIdx.x; j < w; j += NT) sw.mover[j] = sw.head[j] && f.sel[j];
+    __syncthreads();
+    while (swap_round(sw, T, V, ld, w, 0, w) > 0 && !sw.rejected) {
     }
+    const int fail = sw.rejected;
+    int placed = 0;  // selected blocks at the top
+    while (placed < w && sw.mover[placed]) placed += sw.head[placed + 1] ? 1 : 2;
     // standard form for every 2x2 block of the window (swaps leave them in any form)
     for (int k = 0; k + 1 < w;) {
         if (AT(T, ld, k + 1, k) != 0.0) {
