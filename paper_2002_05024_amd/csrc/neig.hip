@@ -1931,13 +1931,13 @@ extern "C" int neig_mlp_grad(int batch, const float *X, const int *a, const int 
     std::lock_guard<std::mutex> lock(g_mutex);
     try {
         DeviceWs &ws = workspace();
-        const int nblk = (batch + MLP_TILE - 1) / MLP_TILE;
+        const int nblk = std::min((batch + MLP_TILE - 1) / MLP_TILE, MLP_GRID);
         grow(&ws.mlp_part, &ws.mlp_part_cap, (size_t)nblk * (MLP_NPARAM + 1));
         float *lossp = ws.mlp_part + (size_t)nblk * MLP_NPARAM;
         hipLaunchKernelGGL(k_mlp_grad, dim3(nblk), dim3(256), 0, stream, theta, X, a, c, w, batch,
                            1.0f / (float)batch, ws.mlp_part, lossp);
         ck(hipGetLastError());
-        hipLaunchKernelGGL(k_mlp_reduce, dim3((MLP_NPARAM + 1 + 255) / 256), dim3(256), 0, stream, ws.mlp_part,
+        hipLaunchKernelGGL(k_mlp_reduce, dim3((MLP_NPARAM + 1 + 63) / 64), dim3(256), 0, stream, ws.mlp_part,
                            lossp, nblk, grad, loss);
         ck(hipGetLastError());
     } catch (const HipFail &f) {
