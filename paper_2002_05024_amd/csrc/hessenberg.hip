@@ -5,20 +5,19 @@
 // A <- (I - V T V^T)^T (A - Y V^T) and the top-part update A <- A - Y V^T.
 //
 // Per panel column (three launches, all on the caller's stream):
-//   k_hrd_a   finish the previous reflector (its v into V, its column of H, the
-//             column Y(:, i-1) = tau (A v - Y u)), then apply the panel's earlier
-//             reflectors to the new column from the right (a -= Y V(j, :)^T) and
-//             form w = V^T a;
-//   k_hrd_b   apply them from the left (a -= V T^T w), build the new reflector
-//             (alpha, scaled norm of the tail, beta, tau), u = V^T v and the new
-//             column of T;
+//   k_hrd_a   finish the previous reflector (beta, tau, u = V^T v, its v into V, its
+//             column of H and of T, the column Y(:, i-1) = tau (A v - Y u)), then
+//             apply the panel's earlier reflectors to the new column from the
+//             right (a -= Y V(j, :)^T) and sum w = V^T a;
+//   k_hrd_b   apply them from the left (a -= V T^T w), and sum the new reflector's
+//             norm and V^T (tail);
 //   k_hrd_gemv  the large matrix-vector product A(:, j+2:n) v over the trailing
 //             part, split over row blocks x column chunks (the memory-bound 20%
 //             of the flops); the partial sums go to a workspace and are added by
 //             the next k_hrd_a.
-// The reductions that end each column kernel (w, the tail norm, u) are done by
-// the last workgroup to finish (a device-scope counter; no workgroup waits for
-// another), in a fixed order, so results do not depend on scheduling.
+// The column kernels leave their sums over the rows (w, the tail norm, u) as
+// partial sums per workgroup, which the workgroups of the next launch add for
+// themselves in a fixed order, so results do not depend on scheduling.
 //
 // Per panel (FP64 matrix-core kernels): k_hrd_skinny forms the thin products
 // A_top V, Y^T V, A_t^T V and Q V (split over the long dimension), k_hrd_reduce
@@ -33,326 +32,383 @@
 
 #define HRD_NB 64        // largest panel width
 #define HRD_THREADS 256
-#define HRD_RB 256       // rows per workgroup in k_hrd_a / k_hrd_b
-#define HRD_GR 512       // rows per workgroup in the GEMV (two per thread)
-#define HRD_GC 256       // vector entries per GEMV workgroup (512 for large trailing blocks)
+#define HRD_GR 512       // rows per workgroup in the large GEMV (two per thread)
+#define HRD_GC 256       // vector entries per GEMV workgroup (512 for the largest trailing blocks)
 #define HRD_GC_MAX 512
 
 struct HrdState {
-    double alpha, beta, tau, scal;
-    double s[HRD_NB];     // T^T w for the current column
-    double u[HRD_NB];     // V^T v of the newest reflector
-    unsigned int count_a, count_b;
+    unsigned long long amax;  // bits of max |A|
+    double alpha;             // the newest column's entry on the subdiagonal
 };
 
 struct HrdArgs {
     double *A;
-    double *V, *Y, *T;     // V, Y: leading dimension ldw; T: HRD_NB x HRD_NB
-    double *part;          // per-workgroup partials, HRD_NB + 2 per workgroup
-    double *zpart;         // GEMV partials, chunk-major, leading dimension ldw
+    double *V, *Y, *T, *Tr;  // V, Y: leading dimension ldw; T: HRD_NB x HRD_NB, Tr its transpose
+    double *wpart, *upart;   // per workgroup: 64 partial entries of V^T a and of V^T (tail)
+    double *spart;           // per 64 rows: scale and scaled sum of squares of the tail
+    double *zpart;           // GEMV partials, chunk-major, leading dimension ldw
     HrdState *st;
     int lda, ldw;
     int n, k0, m, i, jb, nch;  // nch: chunks of the previous GEMV
-    int cw;                    // vector entries per GEMV chunk (HRD_GC or HRD_GC_MAX)
+    int cw;                    // vector entries per GEMV chunk
 };
 
-// Sum x[c] (c < 64) over the 64 lanes of a wavefront by recursive halving:
-// afterwards lane l returns the total of entry l.  63 shuffles.
-template <int S>
-__device__ __forceinline__ void hrd_halve(double (&x)[HRD_NB], int lane) {
-    const bool up = (lane & S) != 0;
+// The vector that the GEMV multiplies is the column's tail times this power of
+// two, so that the products neither overflow nor underflow where A's entries do
+// not; the reflector's own scaling 1 / (alpha - beta) follows in k_hrd_a.
+__device__ __forceinline__ double hrd_scale(const HrdState *st, bool inverse) {
+    int e = (int)(st->amax >> 52) - 1023;
+    if (e == -1023 || e == 1024) e = 0;  // zero or subnormal, or not finite
+    return ldexp(1.0, inverse ? e : -e);
+}
+
+extern "C" __global__ void k_hrd_begin(HrdState *st) {
+    st->amax = 0ull;
+    st->alpha = 0.0;
+}
+
+extern "C" __global__ void __launch_bounds__(HRD_THREADS) k_hrd_amax(const double *A, int lda, int n, HrdState *st) {
+    double mx = 0.0;
+    for (int j = blockIdx.x; j < n; j += gridDim.x)
+        for (int i = threadIdx.x; i < n; i += HRD_THREADS) mx = fmax(mx, fabs(AT(A, lda, i, j)));
+    mx = wave_max(mx);
+    if ((threadIdx.x & 63) == 0) atomicMax(&st->amax, (unsigned long long)__double_as_longlong(mx));
+}
+
+// Sum of x[e] (e < 16) over the 64 lanes of a wavefront: lane l returns the total
+// of entry l % 16.  Halving over the 16 lanes of a row by register moves (mirror,
+// half mirror, exchanges within quads), then across the four rows.
+template <int CTRL, int S>
+__device__ __forceinline__ void hrd_halve(double (&x)[16], bool up) {
 #pragma unroll
     for (int k = 0; k < S; ++k) {
         const double send = up ? x[k] : x[k + S];
         const double keep = up ? x[k + S] : x[k];
-        x[k] = keep + __shfl_xor(send, S);
+        x[k] = keep + dpp_move<CTRL, 0xf>(send, 0.0);
     }
 }
 
-__device__ __forceinline__ double hrd_transpose_sum(double (&x)[HRD_NB], int lane) {
-    hrd_halve<32>(x, lane);
-    hrd_halve<16>(x, lane);
-    hrd_halve<8>(x, lane);
-    hrd_halve<4>(x, lane);
-    hrd_halve<2>(x, lane);
-    hrd_halve<1>(x, lane);
-    return x[0];
+__device__ __forceinline__ double hrd_sum16(double (&x)[16], int lane) {
+    hrd_halve<0x140, 8>(x, (lane & 8) != 0);
+    hrd_halve<0x141, 4>(x, (lane & 4) != 0);
+    hrd_halve<0x4E, 2>(x, (lane & 2) != 0);
+    hrd_halve<0xB1, 1>(x, (lane & 1) != 0);
+    double v = x[0];
+    v += __shfl_xor(v, 16);
+    return v + __shfl_xor(v, 32);
 }
 
-// Column sums over the workgroups' partials (nblk rows of stride HRD_NB + 2)
-// for the first 64 entries, by all 256 threads: thread (c, q) adds the blocks
-// q, q + 4, ... in order, then the four quarter sums are added in order; the
-// totals land in out[0..63].  The order is fixed, so results are reproducible.
-__device__ __forceinline__ void hrd_sum_partials(const double *part, int nblk, double (*red)[HRD_NB],
-                                                 double *out) {
-    const int t = threadIdx.x, c = t & 63, q = t >> 6;
-    double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-    int b = q;
-    for (; b + 12 < nblk; b += 16) {
-        a0 += part[(size_t)b * (HRD_NB + 2) + c];
-        a1 += part[(size_t)(b + 4) * (HRD_NB + 2) + c];
-        a2 += part[(size_t)(b + 8) * (HRD_NB + 2) + c];
-        a3 += part[(size_t)(b + 12) * (HRD_NB + 2) + c];
+// The column kernels.  A workgroup has 64 RG rows, one per lane; wave 4 g + q takes
+// the panel columns q, q + 4, ... of row group g, so a row's 64 entries of V and Y
+// are 16 loads per lane, all in flight at once.  Sums over the rows leave 64
+// partial entries per workgroup in memory, and every workgroup of the next launch
+// adds all of them for itself: no workgroup waits for another within a launch, and
+// the long product k_hrd_gemv, which needs none of these sums, starts right after
+// k_hrd_b.  What bounds them is latency: a round of loads from L2, the sums, a few
+// barriers.  Measured on MI355X, us per column (k_hrd_a, k_hrd_b, the product):
+// order 1000: 7.5 + 5.5 + 3.5, before 15.7 + 15.1 + 14.6 (one thread per row, and
+// the last workgroup to finish added the sums; 512 x 256 tiles in the product);
+// order 8000, whole reduction with Q1: 831 -> 491 ms, of which the products take
+// 273 ms (5 TB/s).  Four row groups per workgroup instead of two on long columns:
+// 12.8 + 8.3 instead of 9.1 + 6.8.
+
+// Column sums over nblk workgroups' partials (stride 64), in a fixed order: wave p
+// adds blocks p, p + NW, ...; out[0..63] in LDS after a barrier by the caller.
+template <int NW>
+__device__ __forceinline__ void hrd_block_sums(const double *part, int nblk, double (*red)[HRD_NB]) {
+    const int c = threadIdx.x & 63, p = threadIdx.x >> 6;
+    double a[4] = {0.0, 0.0, 0.0, 0.0};
+    int b = p;
+    for (; b + 3 * NW < nblk; b += 4 * NW) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) a[u] += part[(size_t)(b + u * NW) * HRD_NB + c];
     }
-    for (; b < nblk; b += 4) a0 += part[(size_t)b * (HRD_NB + 2) + c];
-    red[q][c] = (a0 + a1) + (a2 + a3);
-    __syncthreads();
-    if (t < HRD_NB) out[t] = (red[0][t] + red[1][t]) + (red[2][t] + red[3][t]);
-    __syncthreads();
+    for (; b < nblk; b += NW) a[0] += part[(size_t)b * HRD_NB + c];
+    red[p][c] = (a[0] + a[1]) + (a[2] + a[3]);
 }
 
-// Stage the panel's T (HRD_NB x HRD_NB) in LDS.
-__device__ __forceinline__ void hrd_stage_t(const double *T, double *Ts) {
-    for (int idx = threadIdx.x; idx < HRD_NB * HRD_NB; idx += HRD_THREADS) Ts[idx] = T[idx];
-    __syncthreads();
+template <int NW>
+__device__ __forceinline__ double hrd_add_waves(double (*red)[HRD_NB], int c) {
+    double s = 0.0;
+#pragma unroll
+    for (int p = 0; p < NW; ++p) s += red[p][c];
+    return s;
 }
 
-// (scale, ssq) representation of a sum of squares: value = scale^2 * ssq.
-__device__ __forceinline__ void hrd_ssq_merge(double &sc, double &sq, double sc2, double sq2) {
-    if (sc2 == 0.0) return;
-    if (sc < sc2) {
-        const double r = sc / sc2;
-        sq = sq2 + sq * r * r;
-        sc = sc2;
+// Partial entries 4 e + q of this workgroup (e = lane % 16 of wave 4 g + q) to memory.
+template <int RG>
+__device__ __forceinline__ void hrd_store_part(double v, double *part, double (*red)[HRD_NB], int lane, int q, int g) {
+    if (RG == 1) {
+        if (lane < 16) part[(size_t)blockIdx.x * HRD_NB + 4 * lane + q] = v;
     } else {
-        const double r = sc2 / sc;
-        sq += sq2 * r * r;
+        if (lane < 16) red[g][4 * lane + q] = v;
+        __syncthreads();
+        if (threadIdx.x < HRD_NB) part[(size_t)blockIdx.x * HRD_NB + threadIdx.x] = hrd_add_waves<RG>(red, threadIdx.x);
     }
 }
 
-// Finish reflector i-1 (if any) and apply the panel's earlier reflectors to
-// column j = k0 + i from the right; partial w = V^T a per workgroup; the last
-// workgroup forms s = T^T w.
-extern "C" __global__ void __launch_bounds__(HRD_THREADS) k_hrd_a(HrdArgs p) {
-    __shared__ double vrow[HRD_NB];
-    __shared__ double uprev[HRD_NB];
-    __shared__ double red[HRD_THREADS / 64][HRD_NB];
-    __shared__ int is_last;
-    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-    const int i = p.i;
-    const int r = blockIdx.x * HRD_RB + t;
+// Finish reflector i-1: beta, tau and u = V^T v from the sums of k_hrd_b; its vector
+// into V, its column of H, Y(:, i-1) = tau (A v - Y u), its column of T.  Then apply
+// the panel's earlier reflectors to column j = k0 + i from the right,
+// a -= Y V(i-1, :)^T, and sum V^T a.
+template <int RG>
+__global__ void __launch_bounds__(HRD_THREADS * RG) k_hrd_a(HrdArgs p) {
+    constexpr int NW = 4 * RG;
+    __shared__ double red[NW][HRD_NB];
+    __shared__ double comb[3][4][64 * RG];
+    __shared__ double us[HRD_NB], vs[HRD_NB], coef[3];
+    const int t = threadIdx.x, lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6), q = wave & 3, g = wave >> 2;
+    const int i = p.i, ip = i - 1, j = p.k0 + i;
+    const int lr = g * 64 + lane;
+    const int r = blockIdx.x * 64 * RG + lr;
     const bool in = r < p.m;
-    const size_t g = (size_t)p.k0 + 1 + r;
-    const int j = p.k0 + i;
-    if (t < i - 1) {
-        vrow[t] = AT(p.V, p.ldw, i - 1, t);
-        uprev[t] = p.st->u[t];
-    }
-    __syncthreads();
+    const int rr = in ? r : p.m - 1;
+    const size_t gr = (size_t)p.k0 + 1 + rr;
     const bool last = i == p.jb;  // the panel's last launch only finishes reflector i-1
-    double x[HRD_NB];
+    const int nblk = gridDim.x;
+    // the first wave's part of the reflector: its loads go out before all others
+    double nsc[2], nsq[2], alpha = 0.0, vr = 0.0;
 #pragma unroll
-    for (int c = 0; c < HRD_NB; ++c) x[c] = 0.0;
-    if (in) {
-        // reflector i-1: its vector, its column of H, its column of Y; with one
-        // pass over Y(g, 0:i-1) both Y u and the right update Y V(i-1, :)^T
-        const double scal = p.st->scal, tau = p.st->tau, beta = p.st->beta;
-        const double old = AT(p.A, p.lda, g, j - 1);
-        const double vnew = r < i - 1 ? 0.0 : (r == i - 1 ? 1.0 : old * scal);
-        AT(p.V, p.ldw, r, i - 1) = vnew;
-        if (r >= i - 1) AT(p.A, p.lda, g, j - 1) = (r == i - 1) ? beta : 0.0;
-        const double aj = AT(p.A, p.lda, g, j);  // column j, not yet touched by this panel
-        // the GEMV partials, eight loads in flight, added in a fixed order
-        double z[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-        int ch = 0;
-        for (; ch + 8 <= p.nch; ch += 8) {
-            const double *zp = p.zpart + (size_t)ch * p.ldw + r;
-#pragma unroll
-            for (int u = 0; u < 8; ++u) z[u] += zp[u * (size_t)p.ldw];
-        }
-        for (; ch < p.nch; ++ch) z[0] += p.zpart[(size_t)ch * p.ldw + r];
-        const double y = aj + (((z[0] + z[1]) + (z[2] + z[3])) + ((z[4] + z[5]) + (z[6] + z[7])));
-        double yu = 0.0, yv = 0.0;
-#pragma unroll 8
-        for (int c = 0; c < i - 1; ++c) {
-            const double yc = AT(p.Y, p.ldw, g, c);
-            yu = fma(yc, uprev[c], yu);
-            yv = fma(yc, vrow[c], yv);
-        }
-        const double ycol = tau * (y - yu);
-        AT(p.Y, p.ldw, g, i - 1) = ycol;
-        if (!last) {
-            // right: a -= Y(g, 0:i) V(i-1, 0:i)^T   (V(i-1, i-1) = 1)
-            const double a = aj - (yv + ycol);
-            AT(p.A, p.lda, g, j) = a;
-#pragma unroll
-            for (int c = 0; c < HRD_NB; ++c) {
-                if (c < i - 1) x[c] = AT(p.V, p.ldw, r, c) * a;
-                else if (c == i - 1) x[c] = vnew * a;
-            }
+    for (int e = 0; e < 2; ++e) {
+        const int b = lane + 64 * e;
+        nsc[e] = nsq[e] = 0.0;
+        if (wave == 0 && b < nblk * RG) {
+            nsc[e] = p.spart[2 * b];
+            nsq[e] = p.spart[2 * b + 1];
         }
     }
-    if (last) return;
-    const double ws = hrd_transpose_sum(x, lane);
-    red[wv][lane] = ws;
-    __syncthreads();
-    if (t < HRD_NB) {
-        double s = 0.0;
-#pragma unroll
-        for (int q = 0; q < HRD_THREADS / 64; ++q) s += red[q][t];
-        p.part[(size_t)blockIdx.x * (HRD_NB + 2) + t] = s;
+    if (wave == 0) {
+        alpha = p.st->alpha;
+        vr = AT(p.V, p.ldw, ip, max(min(lane, ip - 1), 0));
     }
-    __threadfence();
-    __syncthreads();
-    if (t == 0) is_last = atomicAdd(&p.st->count_a, 1u) == gridDim.x - 1;
-    __syncthreads();
-    if (!is_last) return;
-    __threadfence();
-    __shared__ double Ts[HRD_NB * HRD_NB];
-    __shared__ double wsum[HRD_NB];
-    hrd_sum_partials(p.part, gridDim.x, red, wsum);
-    hrd_stage_t(p.T, Ts);
-    if (t < i) {
-        // s = T^T w, T upper triangular
-        double s = 0.0;
-        for (int c = 0; c <= t; ++c) s = fma(Ts[c + t * HRD_NB], wsum[c], s);
-        p.st->s[t] = s;
+    double yv[16], vv[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+        // columns from ip on: the last one again, and a zero in its place
+        const int c = 4 * e + q, cc = max(min(c, ip - 1), 0);
+        const double ye = AT(p.Y, p.ldw, gr, cc), ve = AT(p.V, p.ldw, rr, cc);
+        yv[e] = c < ip ? ye : 0.0;
+        vv[e] = c < ip ? ve : 0.0;
     }
-    if (t == 0) p.st->count_a = 0;
-}
-
-// Left application a -= V s of the earlier reflectors, then the reflector of
-// the column's tail: partial scaled sums of squares and u' = V^T tail per
-// workgroup; the last workgroup forms alpha, beta, tau, 1/(alpha - beta), u and
-// the new column of T.
-extern "C" __global__ void __launch_bounds__(HRD_THREADS) k_hrd_b(HrdArgs p) {
-    __shared__ double s[HRD_NB];
-    __shared__ double red[HRD_THREADS / 64][HRD_NB];
-    __shared__ double rsc[HRD_THREADS / 64], rsq[HRD_THREADS / 64];
-    __shared__ int is_last;
-    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-    const int i = p.i;
-    const int r = blockIdx.x * HRD_RB + t;
-    const bool in = r < p.m;
-    const size_t g = (size_t)p.k0 + 1 + r;
-    const int j = p.k0 + i;
-    if (t < i) s[t] = p.st->s[t];
-    __syncthreads();
-    double x[HRD_NB];
+    const double old = AT(p.A, p.lda, gr, j - 1);
+    const double aj = AT(p.A, p.lda, gr, j);  // column j, not yet touched by this panel
+    double tv[16 / RG];  // row `lane` of T, columns wave, wave + NW, ... (used by the first workgroup)
 #pragma unroll
-    for (int c = 0; c < HRD_NB; ++c) x[c] = 0.0;
-    double sc = 0.0, sq = 0.0;
-    if (in) {
-        // the row of V is read once: held in x, then replaced by V(r, c) a
-        double a = AT(p.A, p.lda, g, j);
-        if (i > 0) {
+    for (int e = 0; e < 16 / RG; ++e) {
+        const int c = wave + NW * e;
+        const double te = p.T[lane + max(min(c, ip - 1), 0) * HRD_NB];
+        tv[e] = c < ip ? te : 0.0;
+    }
+    double z = 0.0;
+    {
+        double zz[8];
 #pragma unroll
-            for (int c = 0; c < HRD_NB; ++c)
-                if (c < i) x[c] = AT(p.V, p.ldw, r, c);
-            double acc = 0.0;
-#pragma unroll
-            for (int c = 0; c < HRD_NB; ++c)
-                if (c < i) acc = fma(x[c], s[c], acc);
-            a -= acc;
-            AT(p.A, p.lda, g, j) = a;
+        for (int u = 0; u < 8; ++u) {
+            const int ch = q + 4 * u;
+            const double ze = p.zpart[(size_t)min(ch, p.nch - 1) * p.ldw + rr];
+            zz[u] = ch < p.nch ? ze : 0.0;
         }
-        if (r > i) {
-            if (a != 0.0) {
-                sc = fabs(a);
-                sq = 1.0;
-            }
-#pragma unroll
-            for (int c = 0; c < HRD_NB; ++c) x[c] *= a;
-        } else {
-#pragma unroll
-            for (int c = 0; c < HRD_NB; ++c) x[c] = 0.0;
-        }
+        for (int ch = q + 32; ch < p.nch; ch += 4) zz[0] += p.zpart[(size_t)ch * p.ldw + rr];
+        z = ((zz[0] + zz[1]) + (zz[2] + zz[3])) + ((zz[4] + zz[5]) + (zz[6] + zz[7]));
     }
-    const double us = hrd_transpose_sum(x, lane);
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-        const double sc2 = __shfl_xor(sc, o), sq2 = __shfl_xor(sq, o);
-        hrd_ssq_merge(sc, sq, sc2, sq2);
-    }
-    red[wv][lane] = us;
-    if (lane == 0) {
-        rsc[wv] = sc;
-        rsq[wv] = sq;
-    }
-    __syncthreads();
-    double *mine = p.part + (size_t)blockIdx.x * (HRD_NB + 2);
-    if (t < HRD_NB) {
-        double v = 0.0;
-#pragma unroll
-        for (int q = 0; q < HRD_THREADS / 64; ++q) v += red[q][t];
-        mine[t] = v;
-    }
-    if (t == 0) {
-        double a = 0.0, b = 0.0;
-        for (int q = 0; q < HRD_THREADS / 64; ++q) hrd_ssq_merge(a, b, rsc[q], rsq[q]);
-        mine[HRD_NB] = a;
-        mine[HRD_NB + 1] = b;
-    }
-    __threadfence();
-    __syncthreads();
-    if (t == 0) is_last = atomicAdd(&p.st->count_b, 1u) == gridDim.x - 1;
-    __syncthreads();
-    if (!is_last) return;
-    __threadfence();
-    __shared__ double coef[2];
-    __shared__ double ufin[HRD_NB];
-    __shared__ double usum[HRD_NB];
-    __shared__ double Ts[HRD_NB * HRD_NB];
-    hrd_sum_partials(p.part, gridDim.x, red, usum);
-    hrd_stage_t(p.T, Ts);
-    if (t < 64) {
-        // the tail's scaled sum of squares: lane l merges blocks l, l + 64, ...
-        // in order, then the lanes merge by a fixed butterfly
-        double a = 0.0, b = 0.0;
-        for (int q = t; q < (int)gridDim.x; q += 64) {
-            const double *pq = p.part + (size_t)q * (HRD_NB + 2);
-            hrd_ssq_merge(a, b, pq[HRD_NB], pq[HRD_NB + 1]);
-        }
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) {
-            const double a2 = __shfl_xor(a, o), b2 = __shfl_xor(b, o);
-            hrd_ssq_merge(a, b, a2, b2);
-        }
-        rsc[0] = a;   // every lane holds the same merged pair
-        rsq[0] = b;
-    }
-    __syncthreads();
-    if (t == 0) {
-        const double a = rsc[0], b = rsq[0];
-        const double sigma = a * sqrt(b);
-        const double alpha = AT(p.A, p.lda, (size_t)p.k0 + 1 + i, j);
+    hrd_block_sums<NW>(p.upart, nblk, red);
+    if (wave == 0) {
+        // the tail's norm: scales are powers of two, so merging them is exact
+        double mx = fmax(nsc[0], nsc[1]);
+        for (int b = lane + 128; b < nblk * RG; b += 64) mx = fmax(mx, p.spart[2 * b]);
+        mx = wave_max(mx);
         double beta = alpha, tau = 0.0, scal = 0.0;
-        if (sigma != 0.0) {
-            const double nrm = hypot(alpha, sigma);
+        if (mx > 0.0) {
+            const int em = ilogb(mx);
+            const double inv = ldexp(1.0, -em);
+            double sq = nsq[0] * (nsc[0] * inv) * (nsc[0] * inv) + nsq[1] * (nsc[1] * inv) * (nsc[1] * inv);
+            for (int b = lane + 128; b < nblk * RG; b += 64) {
+                const double f = p.spart[2 * b] * inv;
+                sq += p.spart[2 * b + 1] * f * f;
+            }
+            sq = wave_sum(sq);
+            // the norm with alpha, both scaled to the larger exponent
+            const int ea = alpha != 0.0 && isfinite(alpha) ? ilogb(alpha) : em;
+            const int e = max(ea, em);
+            const double as = ldexp(alpha, -e);
+            const double nrm = ldexp(sqrt(as * as + ldexp(sq, 2 * max(em - e, -600))), e);
             beta = alpha >= 0.0 ? -nrm : nrm;
             tau = (beta - alpha) / beta;
             scal = 1.0 / (alpha - beta);
         }
-        p.st->alpha = alpha;
-        p.st->beta = beta;
-        p.st->tau = tau;
-        p.st->scal = scal;
-        coef[0] = tau;
-        coef[1] = scal;
-    }
-    __syncthreads();
-    if (t < i) {
-        const double u = AT(p.V, p.ldw, i, t) + coef[1] * usum[t];
-        ufin[t] = u;
-        p.st->u[t] = u;
-    }
-    __syncthreads();
-    if (t < HRD_NB) {
-        // column i of T: T(0:i, i) = -tau T(0:i, 0:i) u, T(i, i) = tau, zero below
-        double v = 0.0;
-        if (t < i) {
-            for (int c = t; c < i; ++c) v = fma(Ts[t + c * HRD_NB], ufin[c], v);
-            v *= -coef[0];
-        } else if (t == i) {
-            v = coef[0];
+        vs[lane] = lane < ip ? vr : 0.0;
+        if (lane == 0) {
+            coef[0] = beta;
+            coef[1] = tau;
+            coef[2] = scal;
         }
-        p.T[t + (size_t)i * HRD_NB] = v;
     }
-    if (t == 0) p.st->count_b = 0;
+    __syncthreads();
+    const double beta = coef[0], tau = coef[1], scal = coef[2];
+    if (t < HRD_NB) us[t] = t < ip ? vs[t] + scal * hrd_add_waves<NW>(red, t) : 0.0;
+    __syncthreads();
+    double yu = 0.0, yw = 0.0;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+        yu = fma(yv[e], us[4 * e + q], yu);
+        yw = fma(yv[e], vs[4 * e + q], yw);
+    }
+    comb[0][q][lr] = z;
+    comb[1][q][lr] = yu;
+    comb[2][q][lr] = yw;
+    if (blockIdx.x == 0) {
+        double s = 0.0;
+#pragma unroll
+        for (int e = 0; e < 16 / RG; ++e) {
+            const int c = wave + NW * e;
+            if (c >= lane) s = fma(tv[e], us[c], s);  // us is zero from ip on
+        }
+        red[wave][lane] = s;
+    }
+    __syncthreads();
+    if (blockIdx.x == 0 && t < HRD_NB) {
+        // column i-1 of T: T(0:i-1, i-1) = -tau T(0:i-1, 0:i-1) u, T(i-1, i-1) = tau
+        const double v = t < ip ? -tau * hrd_add_waves<NW>(red, t) : (t == ip ? tau : 0.0);
+        p.T[t + (size_t)ip * HRD_NB] = v;
+        p.Tr[ip + (size_t)t * HRD_NB] = v;
+    }
+    z = (comb[0][0][lr] + comb[0][1][lr]) + (comb[0][2][lr] + comb[0][3][lr]);
+    yu = (comb[1][0][lr] + comb[1][1][lr]) + (comb[1][2][lr] + comb[1][3][lr]);
+    yw = (comb[2][0][lr] + comb[2][1][lr]) + (comb[2][2][lr] + comb[2][3][lr]);
+    const double vnew = r < ip ? 0.0 : (r == ip ? 1.0 : old * scal);
+    const double ycol = tau * ((aj + (z * scal) * hrd_scale(p.st, true)) - yu);
+    const double a = aj - (yw + ycol);  // V(i-1, i-1) = 1
+    if (q == 0 && in) {
+        AT(p.V, p.ldw, r, ip) = vnew;
+        AT(p.Y, p.ldw, gr, ip) = ycol;
+        if (r >= ip) AT(p.A, p.lda, gr, j - 1) = (r == ip) ? beta : 0.0;
+        if (!last) AT(p.A, p.lda, gr, j) = a;
+    }
+    if (last) return;
+    double x[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) x[e] = in ? (4 * e + q == ip ? vnew : vv[e]) * a : 0.0;
+    __syncthreads();  // red is free
+    hrd_store_part<RG>(hrd_sum16(x, lane), p.wpart, red, lane, q, g);
 }
 
-// z(r) = sum over the chunk's entries c of A(k0+1+r, k0+1+c) * scal * a(c),
+// Left application a -= V T^T (V^T a) of the earlier reflectors to column j, then
+// for its reflector: the scaled sum of squares of the tail and V^T (tail).
+template <int RG>
+__global__ void __launch_bounds__(HRD_THREADS * RG) k_hrd_b(HrdArgs p) {
+    constexpr int NW = 4 * RG;
+    __shared__ double red[NW][HRD_NB];
+    __shared__ double comb[4][64 * RG];
+    __shared__ double ws[HRD_NB], ss[HRD_NB];
+    const int t = threadIdx.x, lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6), q = wave & 3, g = wave >> 2;
+    const int i = p.i, j = p.k0 + i;
+    const int lr = g * 64 + lane;
+    const int r = blockIdx.x * 64 * RG + lr;
+    const bool in = r < p.m;
+    const int rr = in ? r : p.m - 1;
+    const size_t gr = (size_t)p.k0 + 1 + rr;
+    double vv[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+        const int c = 4 * e + q;
+        const double ve = AT(p.V, p.ldw, rr, max(min(c, i - 1), 0));
+        vv[e] = c < i ? ve : 0.0;
+    }
+    double a = AT(p.A, p.lda, gr, j);
+    if (i > 0) {
+        double tv[16 / RG];  // column `lane` of T, rows wave, wave + NW, ...
+#pragma unroll
+        for (int e = 0; e < 16 / RG; ++e) {
+            const int c = wave + NW * e;
+            tv[e] = p.Tr[lane + min(c, i - 1) * HRD_NB];  // used for c <= lane < i
+        }
+        hrd_block_sums<NW>(p.wpart, gridDim.x, red);
+        __syncthreads();
+        if (t < HRD_NB) ws[t] = hrd_add_waves<NW>(red, t);
+        __syncthreads();
+        double s = 0.0;
+#pragma unroll
+        for (int e = 0; e < 16 / RG; ++e) {
+            const int c = wave + NW * e;
+            if (c <= lane && lane < i) s = fma(tv[e], ws[c], s);  // s = T^T w, T upper triangular
+        }
+        red[wave][lane] = s;
+        __syncthreads();
+        if (t < HRD_NB) ss[t] = hrd_add_waves<NW>(red, t);
+        __syncthreads();
+        double acc = 0.0;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc = fma(vv[e], ss[4 * e + q], acc);
+        comb[q][lr] = acc;
+        __syncthreads();
+        a -= (comb[0][lr] + comb[1][lr]) + (comb[2][lr] + comb[3][lr]);
+        if (q == 0 && in) AT(p.A, p.lda, gr, j) = a;
+    }
+    if (q == 0 && r == i) p.st->alpha = a;
+    const double tail = (in && r > i) ? a : 0.0;
+    if (q == 0) {
+        const double mx = wave_max(fabs(tail));
+        const double sc = (mx > 0.0 && mx < INFINITY) ? ldexp(1.0, ilogb(mx)) : (mx > 0.0 || tail != tail ? 1.0 : 0.0);
+        const double scl = wave_max(sc);
+        const double y = scl > 0.0 ? tail / scl : 0.0;
+        const double sq = wave_sum(y * y);
+        if (lane == 0) {
+            p.spart[2 * (blockIdx.x * RG + g)] = scl;
+            p.spart[2 * (blockIdx.x * RG + g) + 1] = sq;
+        }
+    }
+    double x[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) x[e] = vv[e] * tail;
+    __syncthreads();  // red is free
+    hrd_store_part<RG>(hrd_sum16(x, lane), p.upart, red, lane, q, g);
+}
+
+// z(r) = sum over the chunk's entries c of A(k0+1+r, k0+1+c) * scale * a(c),
 // a = column j's tail (local entries i+1..m-1).  Grid: row blocks x chunks.
+// k_hrd_gemv_small, for trailing blocks whose large tiles would leave compute units
+// idle: 64 rows per workgroup, the chunk's columns split over its four waves.
+extern "C" __global__ void __launch_bounds__(HRD_THREADS) k_hrd_gemv_small(HrdArgs p) {
+    __shared__ double v[HRD_GC];
+    __shared__ double red[4][64];
+    const int t = threadIdx.x, lane = t & 63;
+    const int q = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int c0 = p.i + 1 + blockIdx.y * p.cw;
+    const int cn = min(p.cw, p.m - c0);
+    const size_t base = (size_t)p.k0 + 1;
+    const int r = blockIdx.x * 64 + lane;
+    const int rr = min(r, p.m - 1);
+    const int per = p.cw >> 2;  // columns per wave, a multiple of 16
+    const int f = q * per, l = min(cn, f + per);
+    const double *col = p.A + (base + c0) * (size_t)p.lda + base + rr;
+    double x[16];
+    const size_t ld = (size_t)p.lda;
+    // the first sixteen columns are on their way while the vector is staged
+#pragma unroll
+    for (int u = 0; u < 16; ++u) x[u] = col[(size_t)min(f + u, cn - 1) * ld];
+    const double scale = hrd_scale(p.st, false);
+    if (t < p.cw) v[t] = t < cn ? AT(p.A, p.lda, base + c0 + t, p.k0 + p.i) * scale : 0.0;
+    __syncthreads();
+    double a0 = 0.0, a1 = 0.0;
+    for (int c = f; c < l; c += 16) {
+#pragma unroll
+        for (int u = 0; u < 16; u += 2) {
+            a0 = fma(c + u < l ? x[u] : 0.0, v[c + u], a0);
+            a1 = fma(c + u + 1 < l ? x[u + 1] : 0.0, v[c + u + 1], a1);
+        }
+        if (c + 16 < l) {
+#pragma unroll
+            for (int u = 0; u < 16; ++u) x[u] = col[(size_t)min(c + 16 + u, cn - 1) * ld];
+        }
+    }
+    red[q][lane] = a0 + a1;
+    __syncthreads();
+    if (t < 64 && r < p.m)
+        p.zpart[(size_t)blockIdx.y * p.ldw + r] = (red[0][t] + red[1][t]) + (red[2][t] + red[3][t]);
+}
+
 extern "C" __global__ void __launch_bounds__(HRD_THREADS) k_hrd_gemv(HrdArgs p) {
     __shared__ double v[HRD_GC_MAX];
     const int t = threadIdx.x;
@@ -360,7 +416,7 @@ extern "C" __global__ void __launch_bounds__(HRD_THREADS) k_hrd_gemv(HrdArgs p) 
     const int cn = min(p.cw, p.m - c0);
     const int j = p.k0 + p.i;
     const size_t base = (size_t)p.k0 + 1;
-    const double scal = p.st->scal;
+    const double scal = hrd_scale(p.st, false);
     for (int u = t; u < cn; u += HRD_THREADS) v[u] = AT(p.A, p.lda, base + c0 + u, j) * scal;
     __syncthreads();
     const int r0 = blockIdx.x * HRD_GR + t, r1 = r0 + HRD_THREADS;
@@ -513,36 +569,60 @@ struct RdArgs {
     int ldo, M, nbc;
 };
 
-// out = (sum_s P_s - X B) T, row by row; 64 rows per workgroup.
+// out = (sum_s P_s - X B) T, 16 rows per workgroup: thread (row, g) sums the
+// partials of columns 4 g.. with eight loads in flight and multiplies by B and T
+// from LDS: 19 us at order 1000, 23 at 8000 (64 rows per workgroup and one load
+// after another: 119 and 136).
 extern "C" __global__ void __launch_bounds__(HRD_THREADS) k_hrd_reduce(RdArgs p) {
-    __shared__ double xs[64 * (HRD_NB + 1)];
+    __shared__ double xs[16][HRD_NB + 1], xr[16][HRD_NB + 1];
+    __shared__ double bt[HRD_NB * HRD_NB];
     const int t = threadIdx.x;
-    const int row = t & 63, cg = t >> 6;
-    const int i = blockIdx.x * 64 + row;
-    const bool in = i < p.M;
-    for (int c = 16 * cg; c < 16 * cg + 16; ++c) {
-        double v = 0.0;
-        if (in && c < p.nbc) {
-            for (int s = 0; s < p.ns; ++s) v += p.P[(size_t)s * p.sp + i + (size_t)c * p.M];
-            if (p.X) {
-                double acc = 0.0;
-                for (int k = 0; k < p.nbc; ++k) acc = fma(AT(p.X, p.ldx, i, k), p.B[k + (size_t)c * HRD_NB], acc);
-                v -= acc;
-            }
+    const int row = t & 15, c0 = 4 * (t >> 4);
+    const int i = blockIdx.x * 16 + row;
+    const int ii = min(i, p.M - 1);
+    double acc[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const double *q = p.P + ii + (size_t)min(c0 + u, p.nbc - 1) * p.M;
+        double s[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+        int k = 0;
+        for (; k + 8 <= p.ns; k += 8) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) s[e] += q[(size_t)(k + e) * p.sp];
         }
-        xs[row * (HRD_NB + 1) + c] = v;
+        for (; k < p.ns; ++k) s[0] += q[(size_t)k * p.sp];
+        acc[u] = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
     }
-    __syncthreads();
-    if (!in) return;
-    for (int c = 16 * cg; c < 16 * cg + 16 && c < p.nbc; ++c) {
-        double v;
-        if (p.T) {
-            v = 0.0;
-            for (int k = 0; k <= c; ++k) v = fma(xs[row * (HRD_NB + 1) + k], p.T[k + (size_t)c * HRD_NB], v);
-        } else {
-            v = xs[row * (HRD_NB + 1) + c];
+    if (p.X) {
+        for (int e = t; e < HRD_NB * HRD_NB; e += HRD_THREADS) bt[e] = p.B[e];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) xr[row][c0 + u] = c0 + u < p.nbc ? AT(p.X, p.ldx, ii, c0 + u) : 0.0;
+        __syncthreads();
+        for (int k = 0; k < p.nbc; ++k) {
+            const double x = xr[row][k];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) acc[u] = fma(-x, bt[k + (c0 + u) * HRD_NB], acc[u]);
         }
-        AT(p.out, p.ldo, i, c) = v;
+        __syncthreads();
+    }
+    if (p.T) {
+        for (int e = t; e < HRD_NB * HRD_NB; e += HRD_THREADS) bt[e] = p.T[e];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) xs[row][c0 + u] = acc[u];
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < 4; ++u) acc[u] = 0.0;
+        for (int k = 0; k < min(c0 + 4, p.nbc); ++k) {
+            const double x = xs[row][k];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (k <= c0 + u) acc[u] = fma(x, bt[k + (c0 + u) * HRD_NB], acc[u]);
+        }
+    }
+    if (i < p.M) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (c0 + u < p.nbc) AT(p.out, p.ldo, i, c0 + u) = acc[u];
     }
 }
 

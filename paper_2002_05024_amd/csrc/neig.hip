@@ -1387,7 +1387,7 @@ void hrd_thin(DeviceWs &ws, double *sk, const double *C, int ldc, int trans, int
     else
         hipLaunchKernelGGL(k_hrd_skinny_n, dim3(rb, nsplit), dim3(HRD_THREADS), 0, s, a);
     RdArgs r{sk, sp, nsplit, X, ldx, B, T, out, ldo, M, nbc};
-    hipLaunchKernelGGL(k_hrd_reduce, dim3(rb), dim3(HRD_THREADS), 0, s, r);
+    hipLaunchKernelGGL(k_hrd_reduce, dim3((M + 15) / 16), dim3(HRD_THREADS), 0, s, r);
 }
 
 // C (M x N) -= L1 R1^T + L2 R2^T
@@ -1404,42 +1404,53 @@ void hessenberg_run(int n, double *A, int lda, double *Q, int ldq, hipStream_t s
     if (n <= 2) return;
     const int NB = HRD_NB;
     const int ldw = (n + 7) & ~7;
-    const size_t nrb_max = (size_t)(n + HRD_RB - 1) / HRD_RB;
-    const size_t nch_max = (size_t)(n + HRD_GC - 1) / HRD_GC;
+    const size_t nrb_max = (size_t)(n + 127) / 128 * 2;  // 64-row groups, whole workgroups of two
+    const size_t nch_max = std::max<size_t>(16, (size_t)(n + HRD_GC - 1) / HRD_GC);
     const size_t sk_cap = ((size_t)128 * ws.cus + (size_t)n + 64) * NB;
-    const size_t need = 4 * (size_t)ldw * NB + 2 * (size_t)NB * NB + nrb_max * (NB + 2) + nch_max * ldw + sk_cap;
+    const size_t need = 4 * (size_t)ldw * NB + 3 * (size_t)NB * NB + nrb_max * (2 * NB + 2) + nch_max * ldw + sk_cap;
     grow(&ws.hrd, &ws.hrd_cap, need);
-    if (!ws.hrd_st) {
-        ck(hipMalloc((void **)&ws.hrd_st, sizeof(HrdState)));
-        ck(hipMemset(ws.hrd_st, 0, sizeof(HrdState)));
-    }
+    if (!ws.hrd_st) ck(hipMalloc((void **)&ws.hrd_st, sizeof(HrdState)));
     double *V = ws.hrd, *Y = V + (size_t)ldw * NB, *P = Y + (size_t)ldw * NB, *Mt = P + (size_t)ldw * NB;
-    double *T = Mt + (size_t)ldw * NB, *Gt = T + (size_t)NB * NB;
-    double *part = Gt + (size_t)NB * NB, *zpart = part + nrb_max * (NB + 2), *sk = zpart + nch_max * ldw;
-    // the two workgroup counters start at zero (the last workgroup of every
-    // column kernel resets its counter; this also clears them after an
-    // interrupted call)
-    ck(hipMemsetAsync(ws.hrd_st, 0, sizeof(HrdState), s));
-    HrdArgs ha{A, V, Y, T, part, zpart, ws.hrd_st, lda, ldw, n, 0, 0, 0, 0, 0, HRD_GC};
+    double *T = Mt + (size_t)ldw * NB, *Tr = T + (size_t)NB * NB, *Gt = Tr + (size_t)NB * NB;
+    double *wpart = Gt + (size_t)NB * NB, *upart = wpart + nrb_max * NB, *spart = upart + nrb_max * NB;
+    double *zpart = spart + 2 * nrb_max, *sk = zpart + nch_max * ldw;
+    hipLaunchKernelGGL(k_hrd_begin, dim3(1), dim3(1), 0, s, ws.hrd_st);
+    hipLaunchKernelGGL(k_hrd_amax, dim3(std::min(n, 4 * ws.cus)), dim3(HRD_THREADS), 0, s, A, lda, n, ws.hrd_st);
+    HrdArgs ha{A, V, Y, T, Tr, wpart, upart, spart, zpart, ws.hrd_st, lda, ldw, n, 0, 0, 0, 0, 0, HRD_GC};
     for (int k0 = 0; k0 < n - 2; k0 += NB) {
         const int jb = std::min(NB, n - 2 - k0);
         const int m = n - k0 - 1;
-        const int nrb = (m + HRD_RB - 1) / HRD_RB;
         ha.k0 = k0;
         ha.m = m;
         ha.jb = jb;
-        // wider GEMV chunks on large trailing blocks: fewer partial sums per row
-        // while the grid still has thousands of workgroups
-        ha.cw = m > 8192 ? HRD_GC_MAX : HRD_GC;
+        // GEMV tiles: 512 x 512 and 512 x 256 while that gives every compute unit
+        // several; below, 64 rows by so many columns that there are about 16 chunks.
+        // (order 1000: 3.5 us a product instead of 14.6 with 512 x 256 tiles).  The
+        // column kernels take 128 rows per workgroup on long columns, so that every
+        // workgroup has at most 64 partial sums to add up to order 8192 (7.8 us for
+        // k_hrd_a with 64 rows at order 4096, 9.1 with 128 above).
+        const bool small = m <= 4096, wide = m > 4096;
+        ha.cw = m > 8192 ? HRD_GC_MAX : (m > 2048 ? HRD_GC : (m > 1024 ? 128 : 64));
         int nch = 0;
         for (int i = 0; i <= jb; ++i) {
             ha.i = i;
             ha.nch = nch;
-            if (i > 0) hipLaunchKernelGGL(k_hrd_a, dim3(nrb), dim3(HRD_THREADS), 0, s, ha);
+            if (i > 0) {
+                if (wide)
+                    hipLaunchKernelGGL(k_hrd_a<2>, dim3((m + 127) / 128), dim3(2 * HRD_THREADS), 0, s, ha);
+                else
+                    hipLaunchKernelGGL(k_hrd_a<1>, dim3((m + 63) / 64), dim3(HRD_THREADS), 0, s, ha);
+            }
             if (i == jb) break;
-            hipLaunchKernelGGL(k_hrd_b, dim3(nrb), dim3(HRD_THREADS), 0, s, ha);
+            if (wide)
+                hipLaunchKernelGGL(k_hrd_b<2>, dim3((m + 127) / 128), dim3(2 * HRD_THREADS), 0, s, ha);
+            else
+                hipLaunchKernelGGL(k_hrd_b<1>, dim3((m + 63) / 64), dim3(HRD_THREADS), 0, s, ha);
             nch = (m - i - 1 + ha.cw - 1) / ha.cw;
-            hipLaunchKernelGGL(k_hrd_gemv, dim3((m + HRD_GR - 1) / HRD_GR, nch), dim3(HRD_THREADS), 0, s, ha);
+            if (small)
+                hipLaunchKernelGGL(k_hrd_gemv_small, dim3((m + 63) / 64, nch), dim3(HRD_THREADS), 0, s, ha);
+            else
+                hipLaunchKernelGGL(k_hrd_gemv, dim3((m + HRD_GR - 1) / HRD_GR, nch), dim3(HRD_THREADS), 0, s, ha);
         }
         const int nt = n - k0 - jb;  // trailing columns k0 + jb .. n-1
         double *Atop = A + (size_t)(k0 + 1) * lda;
