@@ -44,7 +44,8 @@ typedef struct neig_params {
     int ns;        /* shifts per multishift sweep (even)                                */
     int nw;        /* aggressive-early-deflation window size                             */
     int nmin;      /* active blocks of at most nmin rows go to the in-LDS double-shift QR */
-    int chain;     /* bulges per chain (one chase workgroup per chain)                   */
+    int chain;     /* bulges per chain (one chase workgroup per chain); 0..32, a chain has
+                      at most 8                                                           */
     int chase_w;   /* rows/cols of one chase window held in LDS                          */
     int deflation; /* 0: window criterion |spike| <= eps*|lambda| (LAPACK-style);
                       1: norm-stable criterion |spike| <= eps*||H||_F (Section 5)        */

@@ -1,29 +1,46 @@
 // chase.hip -- the window task of the multishift sweep (Section 3.2).
 //
-// One workgroup per diagonal window.  A chain of up to 31 bulges, spaced three
+// One workgroup per diagonal window.  A chain of up to 8 bulges, spaced three
 // rows apart, is chased through the window; at each step every active bulge's
 // 3-element reflector is applied from the left to the window's rows, from the
 // right to the window's columns, and accumulated into the window's orthogonal
-// factor U.  Reflectors of one step act on disjoint index triples, so they
-// commute, and the left and the right phase are each fully parallel.  The work
-// of a phase is a flat list of (bulge, column) or (bulge, row) items, one per
-// thread: a bulge at row pos owns the columns pos..r1 from the left and the rows
-// up to pos+3 (and every row of U) from the right, and since consecutive bulges
-// are three rows apart the per-bulge counts form an arithmetic sequence, so a
-// thread finds its bulge in closed form and no lane idles on a column or row
-// that a bulge does not touch.  The next step's reflectors are not generated in
-// a phase of their own: the item that applies a bulge's right reflection to
-// rows pos+1..pos+3 holds, when it is done, the column that generates the
-// bulge's next reflector (rows pos+1..pos+3 of column pos), and builds it on
-// the spot; another item introduces the bulge that enters at ktop in the next
-// step from its shift polynomial.  Two barriers per step.  The window (and U)
-// live in LDS with odd leading dimensions (no bank conflicts on strided
-// columns); the kernel writes back the window and U^T, which the update kernels
-// apply to the rest of H and to Z (the left/right update tasks).
+// factor U.  The window (and U) live in LDS with odd leading dimensions (no bank
+// conflicts on strided columns); the kernel writes back the window and U^T, which
+// the update kernels apply to the rest of H and to Z (the left/right update
+// tasks).
+//
+// A step is a chain of dependent latencies, and with 12 waves on 4 SIMDs it is
+// also bound by how many instructions the waves issue, so the work is split by
+// who waits for it:
+//
+//  * near: wave b owns bulge b.  It applies its reflector to all
+//    columns from the left (one column per lane), then, after a barrier, from the
+//    right to the rows of the zone only: the rows between the trailing bulge and
+//    the leading one (one row per lane, at most 30).  The lanes of rows
+//    pos+1..pos+3 then hold the column that generates the bulge's next reflector;
+//    every lane of the wave gets it through readlane and computes the reflector,
+//    so it never passes through LDS.  Two barriers per step.  (Two bulges per wave
+//    took 4300 cycles a step against 2000: more shifts run as more chains.)
+//  * far: the rows above the zone and the rows of U see right reflections only, and
+//    nothing in the window waits for them.  Four other waves apply them one batch
+//    of 6 steps late: a lane loads its row's span of columns into registers, applies
+//    the batch's reflectors (bulge by bulge: a bulge's columns lie
+//    right of those of the bulges behind it at every earlier step, so this order
+//    gives the same result), and stores it, with the steps' barriers in between.
+//
+// Measured on MI355X, 8 bulges in 64-row windows: 2030 cycles a step (1780 without
+// the far waves), 3600 when all waves shared all rows and one wave built all
+// reflectors; a launch 69 -> 45 us, the n = 4000 reduction of a dense matrix's form
+// 856 -> 729 ms.  Giving the rows of U and H to one wave (half the reflector reads
+// from LDS) was slower, 3000 cycles: its chain then exceeds the half steps.
 #include "neig_dev.h"
 
-#define CHASE_THREADS 1024
-#define CHASE_MAX_BULGES 32
+#define CHASE_NEAR 8      // waves that own bulges
+#define CHASE_FAR 4       // waves for the far rows
+#define CHASE_THREADS (64 * (CHASE_NEAR + CHASE_FAR))
+#define CHASE_MAX_BULGES CHASE_NEAR
+#define CHASE_BATCH 6     // steps per far batch
+#define CHASE_SPAN (3 * (CHASE_NEAR - 1) + CHASE_BATCH + 2)  // columns of eight bulges' batch
 
 struct ChaseWin {
     int r0, r1;  // reflectors act on rows/cols r0..r1 (U is (r1-r0+1)^2)
@@ -40,30 +57,278 @@ struct ChaseArgs {
     int ldut;  // leading dimension (and slot stride ldut*ldut) of the U^T outputs
 };
 
-// First reflector of the bulge introduced at ktop (shifts of its polynomial
+// Reflector of the bulge introduced at ktop (shifts of its polynomial
 // z^2 - tr z + det, scaled), from the leading 3 x 2 corner of the active block
 // (local index p of row ktop).
-__device__ __forceinline__ Refl chase_intro(const double *Hs, int ldhs, int p, int m3, double tr, double det) {
+__device__ __forceinline__ ReflU chase_intro(const double *Hs, int ldhs, int p, int m3, double tr, double det) {
     const double h00 = AT(Hs, ldhs, p, p), h01 = AT(Hs, ldhs, p, p + 1);
     const double h10 = AT(Hs, ldhs, p + 1, p), h11 = AT(Hs, ldhs, p + 1, p + 1);
     const double h21 = (m3 == 3) ? AT(Hs, ldhs, p + 2, p + 1) : 0.0;
     double sc = fmax(fmax(fabs(h00), fabs(h01)), fmax(fmax(fabs(h10), fabs(h11)), fabs(h21)));
     sc = fmax(sc, fmax(fabs(tr), sqrt(fabs(det))));
     if (sc == 0.0) sc = 1.0;
-    const double aa = h00 / sc, bb = h01 / sc, cc = h10 / sc, dd = h11 / sc, ee = h21 / sc;
-    const double tt = tr / sc, dt = det / (sc * sc);
-    return make_refl(aa * aa + bb * cc - tt * aa + dt, cc * (aa + dd - tt), cc * ee);
+    const double rs = 1.0 / sc;
+    const double aa = h00 * rs, bb = h01 * rs, cc = h10 * rs, dd = h11 * rs, ee = h21 * rs;
+    const double tt = tr * rs, dt = det * rs * rs;
+    return refl_u(gen_vec(aa * aa + bb * cc - tt * aa + dt, cc * (aa + dd - tt), cc * ee));
+}
+
+// One batch of reflectors c[step][bulge] on one far row (on: this lane has one) of M
+// (ncol columns); cfirst is the column of bulge 0 at the batch's first step.  full:
+// a full batch of steps runs meanwhile, and its 48 reflectors are spread over its
+// 12 half steps; else no barrier is met here.
+template <bool full>
+__device__ __forceinline__ void chase_far(double *M, int ldm, int ncol, int row, bool on, int cfirst,
+                                          const double (*c)[CHASE_MAX_BULGES][4]) {
+    const int c0 = cfirst - 3 * (CHASE_NEAR - 1);
+    const bool inside = c0 >= 0 && c0 + CHASE_SPAN <= ncol;
+    double x[CHASE_SPAN];
+    double *p = M + row + (ptrdiff_t)c0 * ldm;
+    double f[4][4];  // the next four reflectors
+    auto fetch = [&](int u) __attribute__((always_inline)) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                f[e][v] = c[(u + e) % CHASE_BATCH][(u + e) / CHASE_BATCH][v];
+    };
+    fetch(0);
+    if (inside) {
+        if (on) {
+#pragma unroll
+            for (int k = 0; k < CHASE_SPAN; ++k) x[k] = p[(ptrdiff_t)k * ldm];
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < CHASE_SPAN; ++k) {
+            x[k] = 0.0;
+            if ((unsigned)(c0 + k) < (unsigned)ncol && on) x[k] = p[(ptrdiff_t)k * ldm];
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < CHASE_NEAR * CHASE_BATCH; u += 4) {
+        double h[4][4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) h[e][v] = f[e][v];
+        // four reflectors are read ahead, and no more (left alone, the compiler
+        // reads all of them first and runs out of registers)
+        if (u + 4 < CHASE_NEAR * CHASE_BATCH) fetch(u + 4);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int k = 3 * (CHASE_NEAR - 1 - (u + e) / CHASE_BATCH) + (u + e) % CHASE_BATCH;
+            const double t = h[e][0] * fma(h[e][1], x[k], fma(h[e][2], x[k + 1], h[e][3] * x[k + 2]));
+            x[k] = fma(t, h[e][1], x[k]);
+            x[k + 1] = fma(t, h[e][2], x[k + 1]);
+            x[k + 2] = fma(t, h[e][3], x[k + 2]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        // the last barrier comes after the stores
+        if (full && u + 4 < CHASE_NEAR * CHASE_BATCH) __builtin_amdgcn_s_barrier();
+    }
+    // the values exist from here on (else the compiler moves their arithmetic into
+    // the branches of the stores)
+#pragma unroll
+    for (int k = 0; k < CHASE_SPAN; ++k) asm volatile("" : "+v"(x[k]));
+    if (inside) {
+        if (on) {
+#pragma unroll
+            for (int k = 0; k < CHASE_SPAN; ++k) p[(ptrdiff_t)k * ldm] = x[k];
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < CHASE_SPAN; ++k)
+            if ((unsigned)(c0 + k) < (unsigned)ncol && on) p[(ptrdiff_t)k * ldm] = x[k];
+    }
+    if (full) __syncthreads();
+}
+
+// A three-row reflector from the left on one column (if on), e its first entry.
+__device__ __forceinline__ void chase_left3(double *e, bool on, const ReflU &r) {
+    if (on) {
+        const double x0 = e[0], x1 = e[1], x2 = e[2];
+        const double s = r.q * fma(r.u0, x0, fma(r.u1, x1, r.u2 * x2));
+        e[0] = fma(s, r.u0, x0);
+        e[1] = fma(s, r.u1, x1);
+        e[2] = fma(s, r.u2, x2);
+    }
+}
+
+// A three-row reflector from the right on the zone's rows up to pos+3 (lane lx holds
+// row pos+1, e its entry in column pos), and the bulge's next reflector from what
+// column pos then holds in rows pos+1..pos+3.
+__device__ __forceinline__ void chase_right3(double *e, int ld, int lane, int lx, ReflU &r) {
+    const bool on = lane <= lx + 2;
+    double x0 = 0.0, x1 = 0.0, x2 = 0.0;
+    if (on) {
+        x0 = e[0];
+        x1 = e[ld];
+        x2 = e[2 * ld];
+    }
+    const double s = r.q * fma(r.u0, x0, fma(r.u1, x1, r.u2 * x2));
+    x0 = fma(s, r.u0, x0);
+    x1 = fma(s, r.u1, x1);
+    x2 = fma(s, r.u2, x2);
+    const GenVec g = gen_vec(lane_value(x0, lx), lane_value(x0, lx + 1), lane_value(x0, lx + 2));
+    if (on) {
+        e[ld] = x1;
+        e[2 * ld] = x2;
+    }
+    r = refl_u(g);
+    x0 = pick(lane == lx, r.beta, pick(lane > lx, 0.0, x0));
+    if (on) e[0] = x0;
+}
+
+// The near waves' part of one window: wave b chases bulge b.
+__device__ __forceinline__ void chase_near(double *Hs, int ldhs, int mb, int b0, const ChaseWin &W, int ktop, int kbot,
+                                           const double *poly, double (*cq)[CHASE_BATCH][CHASE_MAX_BULGES][4], int b) {
+    const int lane = threadIdx.x & 63;
+    const bool wide = W.r1 - W.r0 >= 64;
+    int pos = ktop + W.t0 - 3 * b;
+    bool act = b < W.nb && pos >= ktop && pos <= kbot - 1;
+    ReflU r{0.0, 0.0, 0.0, 0.0, 0.0};
+    if (act) {  // the reflector of the window's first step
+        const int p = pos - b0, m3 = (pos <= kbot - 2) ? 3 : 2;
+        if (pos == ktop) {
+            r = chase_intro(Hs, ldhs, p, m3, poly[2 * b], poly[2 * b + 1]);
+        } else {
+            double *c = &AT(Hs, ldhs, p, p - 1);
+            r = refl_u(gen_vec(c[0], c[1], m3 == 3 ? c[2] : 0.0));
+            if (lane < m3) c[lane] = lane == 0 ? r.beta : 0.0;
+        }
+    }
+    __syncthreads();
+    const int c0 = W.r0 - b0 + lane;  // this lane's (first) column
+    int tb = W.t0, buf = 0, steps = 0;
+    for (;; tb += CHASE_BATCH, buf ^= 1) {
+        steps = min(CHASE_BATCH, W.t1 - tb);
+        const int z0 = max(W.r0, ktop + tb - 3 * (W.nb - 1)) - b0;  // the zone's first row
+        if (act && tb + CHASE_BATCH < W.t1 && pos + CHASE_BATCH + 2 <= kbot) {
+            // the bulge goes through all steps of the batch and one more inside the
+            // active block: no case distinctions in the steps
+            int p = pos - b0;
+            double *el = Hs + p + c0 * ldhs, *er = Hs + z0 + lane + p * ldhs, *c = cq[buf][0][b];
+#pragma unroll 1
+            for (int s = 0; s < CHASE_BATCH; ++s) {
+                chase_left3(el, c0 >= p && c0 < mb, r);
+                if (wide) chase_left3(el + 64 * ldhs, c0 + 64 >= p && c0 + 64 < mb, r);
+                if (lane == 0) {
+                    c[0] = r.q; c[1] = r.u0; c[2] = r.u1; c[3] = r.u2;
+                }
+                __syncthreads();
+                chase_right3(er, ldhs, lane, p + 1 - z0, r);
+                __syncthreads();
+                ++p;
+                ++el;
+                er += ldhs;
+                c += 4 * CHASE_MAX_BULGES;
+            }
+            pos += CHASE_BATCH;
+            continue;
+        }
+        for (int t = tb; t < tb + steps; ++t) {
+            const bool more = t + 1 < W.t1;
+            const int p = pos - b0, lx = p + 1 - z0;
+            const bool three = pos <= kbot - 2;
+            // left: rows pos..pos+2 of columns pos..r1, one column per lane
+            if (act) {
+                double *e = Hs + p + c0 * ldhs;
+                if (three) {
+                    chase_left3(e, c0 >= p && c0 < mb, r);
+                    if (wide) chase_left3(e + 64 * ldhs, c0 + 64 >= p && c0 + 64 < mb, r);
+                } else {
+                    for (int c = c0; c < mb; c += 64, e += 64 * ldhs)
+                        if (c >= p) {
+                            const double s = r.q * fma(r.u0, e[0], r.u1 * e[1]);
+                            e[0] = fma(s, r.u0, e[0]);
+                            e[1] = fma(s, r.u1, e[1]);
+                        }
+                }
+            }
+            if (lane == 0) {
+                double *c = cq[buf][t - tb][b];
+                c[0] = r.q; c[1] = r.u0; c[2] = r.u1; c[3] = r.u2;
+            }
+            __syncthreads();
+            // right: the zone's rows up to pos+3 of columns pos..pos+2; the next reflector
+            double *e = Hs + z0 + lane + p * ldhs;
+            if (act && more && pos + 3 <= kbot) {
+                chase_right3(e, ldhs, lane, lx, r);
+            } else if (act) {
+                const bool on = z0 + lane <= min(pos + 3, kbot) - b0;
+                const bool build = more && pos + 1 <= kbot - 1;
+                double x0 = 0.0, x1 = 0.0, x2 = 0.0;
+                if (on) {
+                    x0 = e[0];
+                    x1 = e[ldhs];
+                    if (three) x2 = e[2 * ldhs];
+                }
+                const double s = r.q * fma(r.u0, x0, fma(r.u1, x1, r.u2 * x2));
+                x0 = fma(s, r.u0, x0);
+                x1 = fma(s, r.u1, x1);
+                x2 = fma(s, r.u2, x2);
+                if (on) {
+                    if (!(build && lane >= lx)) e[0] = x0;
+                    e[ldhs] = x1;
+                    if (three) e[2 * ldhs] = x2;
+                }
+                if (build) {  // pos + 3 > kbot: rows pos+1, pos+2 of column pos
+                    r = refl_u(gen_vec(lane_value(x0, lx), lane_value(x0, lx + 1), 0.0));
+                    if (on && lane >= lx) e[0] = lane == lx ? r.beta : 0.0;
+                }
+            }
+            ++pos;
+            act = more && b < W.nb && pos >= ktop && pos <= kbot - 1;
+            if (!act) r.q = r.u0 = r.u1 = r.u2 = 0.0;
+            __syncthreads();
+            if (act && pos == ktop)  // enters with the next step
+                r = chase_intro(Hs, ldhs, ktop - b0, (ktop <= kbot - 2) ? 3 : 2, poly[2 * b], poly[2 * b + 1]);
+        }
+        if (tb + CHASE_BATCH >= W.t1) break;
+    }
+    // the rest of the last batch
+    for (int s = steps; s < CHASE_BATCH; ++s)
+        if (lane < 4) cq[buf][s][b][lane] = 0.0;
+}
+
+// The far waves' part: while batch j runs, batch j - 1 is applied.
+__device__ __forceinline__ void chase_far_rows(double *Hs, int ldhs, int mb, double *Us, int ldus, int b0,
+                                               const ChaseWin &W, int ktop,
+                                               double (*cq)[CHASE_BATCH][CHASE_MAX_BULGES][4], int f) {
+    const int lane = threadIdx.x & 63;
+    const int w = W.r1 - W.r0 + 1;
+    const bool isU = (f & 1) == 0;
+    const int row = lane + 64 * (f >> 1);
+    __syncthreads();
+    int rows = 0, cfirst = 0;  // of the batch that is still to be applied
+    for (int tb = W.t0;; tb += CHASE_BATCH) {
+        const int steps = max(0, min(CHASE_BATCH, W.t1 - tb));
+        const double(*c)[CHASE_MAX_BULGES][4] = cq[(((tb - W.t0) / CHASE_BATCH) & 1) ^ 1];
+        double *M = isU ? Us : Hs;
+        const int ldm = isU ? ldus : ldhs, ncol = isU ? w : mb;
+        const bool any = rows > 64 * (f >> 1);
+        if (any && steps == CHASE_BATCH) {
+            chase_far<true>(M, ldm, ncol, row, row < rows, cfirst, c);
+        } else {
+            // one barrier when no step follows: the last batch's reflectors are complete
+            for (int h = 0; h < max(1, 2 * steps); ++h) __syncthreads();
+            if (any) chase_far<false>(M, ldm, ncol, row, row < rows, cfirst, c);
+        }
+        if (steps == 0) break;
+        const int z0 = max(W.r0, ktop + tb - 3 * (W.nb - 1)) - b0;
+        rows = isU ? w : z0;
+        cfirst = ktop + tb - (isU ? W.r0 : b0);
+    }
 }
 
 extern "C" __global__ void __launch_bounds__(CHASE_THREADS)
 k_chase(double *H, int ldh, const double *poly, double *Ut, ChaseArgs a) {
     extern __shared__ double lds[];
-    // reflectors of the current and of the next step (index: step parity)
-    __shared__ double rtau[2][CHASE_MAX_BULGES], rv1[2][CHASE_MAX_BULGES], rv2[2][CHASE_MAX_BULGES];
-    __shared__ int rm3[2][CHASE_MAX_BULGES];
-
+    __shared__ double cq[2][CHASE_BATCH][CHASE_MAX_BULGES][4];  // two batches' reflectors (q, u0, u1, u2)
     const ChaseWin W = a.win[blockIdx.x];
     const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ktop = a.ktop, kbot = a.kbot;
     const int r0 = W.r0, r1 = W.r1;
     const int b0 = (r0 > 0) ? r0 - 1 : 0;
@@ -72,7 +337,6 @@ k_chase(double *H, int ldh, const double *poly, double *Ut, ChaseArgs a) {
     const int ldhs = mb | 1, ldus = w | 1;
     double *Hs = lds;
     double *Us = lds + (size_t)mb * ldhs;
-    const int nb = W.nb;
     const double *mypoly = poly + 2 * (size_t)W.chain * a.nbc;
 
     for (int idx = tid; idx < mb * mb; idx += CHASE_THREADS) {
@@ -84,160 +348,15 @@ k_chase(double *H, int ldh, const double *poly, double *Ut, ChaseArgs a) {
         AT(Us, ldus, i, j) = (i == j) ? 1.0 : 0.0;
     }
     __syncthreads();
-
-    // reflectors of the window's first step (one thread per bulge)
-    if (tid < CHASE_MAX_BULGES) {
-        const int b = tid, buf = W.t0 & 1;
-        const int pos = ktop + W.t0 - 3 * b;
-        if (b < nb && pos >= ktop && pos <= kbot - 1) {
-            const int m3 = (pos <= kbot - 2) ? 3 : 2;
-            const int p = pos - b0;
-            Refl r;
-            if (pos == ktop) {
-                r = chase_intro(Hs, ldhs, p, m3, mypoly[2 * b], mypoly[2 * b + 1]);
-            } else {
-                r = make_refl(AT(Hs, ldhs, p, p - 1), AT(Hs, ldhs, p + 1, p - 1),
-                              (m3 == 3) ? AT(Hs, ldhs, p + 2, p - 1) : 0.0);
-                AT(Hs, ldhs, p, p - 1) = r.beta;
-                AT(Hs, ldhs, p + 1, p - 1) = 0.0;
-                if (m3 == 3) AT(Hs, ldhs, p + 2, p - 1) = 0.0;
-            }
-            rtau[buf][b] = r.tau; rv1[buf][b] = r.v1; rv2[buf][b] = (m3 == 3) ? r.v2 : 0.0;
-            rm3[buf][b] = m3;
-        }
+    // both kinds of waves meet the same barriers: one before the first step, two
+    // per step, one after the last
+    if (wave < CHASE_NEAR) {
+        chase_near(Hs, ldhs, mb, b0, W, ktop, kbot, mypoly, cq, wave);
+        __syncthreads();
+    } else {
+        chase_far_rows(Hs, ldhs, mb, Us, ldus, b0, W, ktop, cq, wave - CHASE_NEAR);
     }
     __syncthreads();
-
-    const int wave = tid / 64, lane = tid & 63;
-    constexpr int NWAVE = CHASE_THREADS / 64;
-    for (int t = W.t0; t < W.t1; ++t) {
-        const int cur = t & 1, nxt = cur ^ 1;
-        // active bulges blo..bhi: ktop <= pos_b = ktop + t - 3 b <= kbot - 1
-        const int bhi = min(nb - 1, t / 3);
-        const int lag = t - (kbot - 1 - ktop);
-        const int blo = (lag > 0) ? (lag + 2) / 3 : 0;
-        const int na = bhi - blo + 1;
-        const int ptop = ktop + t - 3 * blo;  // row of the leading active bulge
-        const bool more = t + 1 < W.t1;
-
-        // left: bulge k (b = blo + k) on rows pos..pos+m3-1 of columns pos..r1;
-        // one wave per bulge, one column per lane
-        for (int k = wave; k < na; k += NWAVE) {
-            const int b = blo + k;
-            const int p = ptop - 3 * k - b0;
-            const double tau = rtau[cur][b], v1 = rv1[cur][b], v2 = rv2[cur][b];
-            const bool three = rm3[cur][b] == 3;
-            for (int jl = p + lane; jl < mb; jl += 64) {
-                double *c = &AT(Hs, ldhs, p, jl);
-                const double x0 = c[0], x1 = c[1], x2 = three ? c[2] : 0.0;
-                const double s = tau * (x0 + v1 * x1 + v2 * x2);
-                c[0] = x0 - s;
-                c[1] = x1 - s * v1;
-                if (three) c[2] = x2 - s * v2;
-            }
-        }
-        __syncthreads();
-
-        // right: the last wave holds the leaders (lane k: rows pos+1..min(pos+3,
-        // kbot) of bulge blo + k, which then builds the bulge's next reflector)
-        // and introduces the bulge that enters at ktop in the next step (lane
-        // na); the other waves take 64-row chunks of the rest: every row of U
-        // for each bulge, then rows b0..pos of H
-        if (wave == NWAVE - 1) {
-            const int bin = (t + 1) / 3;  // bulge entering at step t + 1, if any
-            const bool intro = more && ((t + 1) % 3 == 0) && bin < nb;
-            if (lane < na) {
-                const int b = blo + lane;
-                const int pos = ptop - 3 * lane;
-                const int p = pos - b0;
-                const double tau = rtau[cur][b], v1 = rv1[cur][b], v2 = rv2[cur][b];
-                const bool three = rm3[cur][b] == 3;
-                const int nr = min(pos + 3, kbot) - pos;  // rows pos+1..pos+nr
-                double y[3][3] = {{0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}};
-#pragma unroll
-                for (int q = 0; q < 3; ++q) {
-                    if (q < nr) {
-                        y[q][0] = AT(Hs, ldhs, p + 1 + q, p);
-                        y[q][1] = AT(Hs, ldhs, p + 1 + q, p + 1);
-                        y[q][2] = three ? AT(Hs, ldhs, p + 1 + q, p + 2) : 0.0;
-                    }
-                }
-#pragma unroll
-                for (int q = 0; q < 3; ++q) {
-                    const double s = tau * (y[q][0] + v1 * y[q][1] + v2 * y[q][2]);
-                    y[q][0] -= s;
-                    y[q][1] -= s * v1;
-                    y[q][2] -= s * v2;
-                }
-                if (more && pos + 1 <= kbot - 1) {
-                    const int m3n = (pos + 1 <= kbot - 2) ? 3 : 2;
-                    const Refl r = make_refl(y[0][0], y[1][0], (m3n == 3) ? y[2][0] : 0.0);
-                    y[0][0] = r.beta;
-                    y[1][0] = 0.0;
-                    if (m3n == 3) y[2][0] = 0.0;
-                    rtau[nxt][b] = r.tau; rv1[nxt][b] = r.v1; rv2[nxt][b] = (m3n == 3) ? r.v2 : 0.0;
-                    rm3[nxt][b] = m3n;
-                }
-#pragma unroll
-                for (int q = 0; q < 3; ++q) {
-                    if (q < nr) {
-                        AT(Hs, ldhs, p + 1 + q, p) = y[q][0];
-                        AT(Hs, ldhs, p + 1 + q, p + 1) = y[q][1];
-                        if (three) AT(Hs, ldhs, p + 1 + q, p + 2) = y[q][2];
-                    }
-                }
-            } else if (lane == na && intro) {
-                const int m3 = (ktop <= kbot - 2) ? 3 : 2;
-                const Refl r = chase_intro(Hs, ldhs, ktop - b0, m3, mypoly[2 * bin], mypoly[2 * bin + 1]);
-                rtau[nxt][bin] = r.tau; rv1[nxt][bin] = r.v1; rv2[nxt][bin] = (m3 == 3) ? r.v2 : 0.0;
-                rm3[nxt][bin] = m3;
-            }
-        } else if (na > 0) {
-            const int uc = (w + 63) >> 6;                 // U chunks per bulge
-            const int hc1 = ptop - b0 + 1;                // H rows b0..pos of the leading bulge
-            // bulges k < m2 have more than 64 such rows (two chunks)
-            const int m2 = min(na, max(0, (hc1 - 64 + 2) / 3));
-            const int ntask = na * uc + na + m2;
-            for (int task = wave; task < ntask; task += NWAVE - 1) {
-                int k, row0, nrow, pc;
-                double *M;
-                int ldm;
-                if (task < na * uc) {
-                    k = task / uc;
-                    row0 = (task - k * uc) * 64;
-                    pc = ptop - 3 * k - r0;
-                    // U starts as I and each bulge passing a row moves its first
-                    // nonzero column left by at most 2, so rows below pc + 2 + 2 nb
-                    // are still zero in columns pc..pc+2: nothing to do there
-                    nrow = min(w, pc + 3 + 2 * nb);
-                    if (row0 >= nrow) continue;
-                    M = Us; ldm = ldus;
-                } else {
-                    const int h = task - na * uc;
-                    int c;
-                    if (h < 2 * m2) { k = h >> 1; c = h & 1; }
-                    else { k = h - m2; c = 0; }
-                    row0 = c * 64;
-                    nrow = hc1 - 3 * k;
-                    pc = ptop - 3 * k - b0;
-                    M = Hs; ldm = ldhs;
-                }
-                const int b = blo + k;
-                const double tau = rtau[cur][b], v1 = rv1[cur][b], v2 = rv2[cur][b];
-                const bool three = rm3[cur][b] == 3;
-                const int row = row0 + lane;
-                if (row < nrow) {
-                    double *e = &AT(M, ldm, row, pc);
-                    const double x0 = e[0], x1 = e[ldm], x2 = three ? e[2 * ldm] : 0.0;
-                    const double s = tau * (x0 + v1 * x1 + v2 * x2);
-                    e[0] = x0 - s;
-                    e[ldm] = x1 - s * v1;
-                    if (three) e[2 * ldm] = x2 - s * v2;
-                }
-            }
-        }
-        __syncthreads();
-    }
 
     // write back what the window changed: columns r0..r1 (rows b0..r1), the three
     // entries of column b0 below r0, and U^T

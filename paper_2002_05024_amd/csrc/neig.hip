@@ -81,6 +81,7 @@ std::vector<PolicySample> g_policy_log;
 
 constexpr int kMaxDevices = 64;
 constexpr int kStatusInts = 64;
+constexpr int kChainParamMax = 32;   // largest value of the parameter chain (chains have at most CHASE_MAX_BULGES)
 constexpr int kOverlapMinN = 8192;  // automatic overlap of sweep updates from this order on
 
 template <class T>
@@ -273,7 +274,7 @@ class Solver {
         nsmall_ = ws_.small_max;
         nmin_ = p_.nmin > 0 ? std::min(p_.nmin, nsmall_) : nsmall_;
         wchase_ = p_.chase_w > 0 ? std::min(p_.chase_w, ws_.chase_max) : ws_.chase_max;
-        nbc_ = p_.chain > 0 ? p_.chain : 16;
+        nbc_ = p_.chain > 0 ? p_.chain : CHASE_MAX_BULGES;
         nbc_ = std::max(1, std::min(nbc_, std::min(CHASE_MAX_BULGES, (wchase_ - 2) / 3)));
         maxit_ = p_.maxit > 0 ? p_.maxit : 30 * std::max(10, n);
         nibble_ = p_.nibble > 0 ? p_.nibble : 14;
@@ -1991,7 +1992,7 @@ extern "C" int neig_set_params(const neig_params *p) {
     if (p->ns < 0 || p->ns % 2) return -1;
     if (p->nw < 0) return -2;
     if (p->nmin < 0) return -3;
-    if (p->chain < 0 || p->chain > CHASE_MAX_BULGES) return -4;
+    if (p->chain < 0 || p->chain > kChainParamMax) return -4;
     if (p->chase_w < 0 || (p->chase_w > 0 && p->chase_w < 8)) return -5;
     if (p->deflation < 0 || p->deflation > 1) return -6;
     if (p->maxit < 0) return -7;
