@@ -1,6 +1,6 @@
 // batched.hip -- many independent Schur reductions in one persistent launch.
 //
-// Each workgroup (4 waves) takes problems from a device work queue (largest
+// Each workgroup (12 waves) takes problems from a device work queue (largest
 // first) and runs the whole method of Section 3.2 on its problem: splitting at
 // negligible subdiagonals, the in-LDS double-shift QR for small blocks,
 // aggressive early deflation on the trailing window, and single-chain
@@ -9,10 +9,23 @@
 // strips of H and Z in HBM with FP64 matrix-core instructions.  All control
 // decisions are taken on the device, so one launch covers the whole batch and
 // can be captured in a graph.  Parallelism comes from the batch: one problem per
-// CU at a time.
+// CU at a time (a window and its factor take the CU's whole LDS).
+//
+// A batch ends with its largest problem, so what bounds it is the time of one
+// problem on one CU.  Measured on MI355X, 512 problems of order 32 to 1024: 515 ms
+// with 4 waves (window chasing in three phases, 14200 cycles a step of 16 bulges;
+// updates through a staged tile, 1.06 million cycles a window), 234 ms now:
+//  * the windows are chased by the sweep kernel's code (chase.hip: 2550 cycles a step
+//    of 8 bulges), so the workgroup has its 12 waves;
+//  * a factor is applied by each wave on its own, sixteen rows or columns at a time,
+//    straight from memory into the matrix cores' layout and back (260 thousand cycles
+//    a window; 435 thousand before the phases were functions of their own).
+// What is left is the window QR and the spike test (half the time, one wave's
+// chain of dependent steps) and, while all CUs work, the passes over H and Z.
 #include "neig_dev.h"
 
-#define B_MAX_BULGES 16
+#define BT CHASE_THREADS  // threads per workgroup
+#define B_MAX_BULGES 16   // per sweep
 #define B_NBUCKET 6
 
 struct BProb {
@@ -40,36 +53,53 @@ struct BArgs {
     int criterion, nibble, exc, maxit_factor;
 };
 
+// What a problem's steps hand on to each other: the Ritz values of the last AED
+// window, and the polynomials (trace, determinant) of the sweep's shift pairs.
+struct BShifts {
+    double rr[NEIG_SMALL_MAX], ri[NEIG_SMALL_MAX];
+    double poly[2 * B_MAX_BULGES];
+    int nritz, nsh;
+};
+
+__device__ __forceinline__ BShifts &batch_shifts() {
+    __shared__ BShifts s;
+    return s;
+}
+
 // ---------------------------------------------------------------- workgroup helpers
 
 // ||H||_F over the Hessenberg part, zeros below the subdiagonal; false on NaN/Inf.
 __device__ __forceinline__ bool wg_prep(double *H, int ldh, int n, double *hnorm) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     double mx = 0.0;
     int bad = 0;
-    for (long long idx = threadIdx.x; idx < (long long)n * n; idx += NT) {
-        const int i = (int)(idx % n), j = (int)(idx / n);
-        if (i > j + 1) {
-            AT(H, ldh, i, j) = 0.0;
-        } else {
-            const double v = AT(H, ldh, i, j);
-            if (!isfinite(v)) bad = 1;
-            else mx = fmax(mx, fabs(v));
+    for (int j = wave; j < n; j += BT / 64) {
+        double *c = &AT(H, ldh, 0, j);
+        for (int i = lane; i < n; i += 64) {
+            if (i > j + 1) {
+                c[i] = 0.0;
+            } else {
+                const double v = c[i];
+                if (!isfinite(v)) bad = 1;
+                else mx = fmax(mx, fabs(v));
+            }
         }
     }
-    mx = block_reduce(mx, true);
-    const double anybad = block_reduce((double)bad, true);
+    mx = block_reduce<BT>(mx, true);
+    const double anybad = block_reduce<BT>((double)bad, true);
     if (anybad != 0.0) return false;
     double ssq = 0.0;
     if (mx > 0.0) {
-        for (long long idx = threadIdx.x; idx < (long long)n * n; idx += NT) {
-            const int i = (int)(idx % n), j = (int)(idx / n);
-            if (i <= j + 1) {
-                const double v = AT(H, ldh, i, j) / mx;
+        for (int j = wave; j < n; j += BT / 64) {
+            const double *c = &AT(H, ldh, 0, j);
+            const int last = min(j + 1, n - 1);
+            for (int i = lane; i <= last; i += 64) {
+                const double v = c[i] / mx;
                 ssq += v * v;
             }
         }
     }
-    ssq = block_reduce(ssq, false);
+    ssq = block_reduce<BT>(ssq, false);
     *hnorm = mx * sqrt(ssq);
     return true;
 }
@@ -77,267 +107,201 @@ __device__ __forceinline__ bool wg_prep(double *H, int ldh, int n, double *hnorm
 // Largest k in [1, kbot] whose subdiagonal is negligible (zeroed), else 0.
 __device__ __forceinline__ int wg_scan(double *H, int ldh, int kbot, double hnorm, double smlnum) {
     double best = 0.0;
-    for (int k = 1 + (int)threadIdx.x; k <= kbot; k += NT) {
+    for (int k = 1 + (int)threadIdx.x; k <= kbot; k += BT) {
         const double sub = AT(H, ldh, k, k - 1);
         if (sub == 0.0 || negligible_sub(sub, AT(H, ldh, k - 1, k - 1), AT(H, ldh, k, k), hnorm, smlnum)) {
             if (sub != 0.0) AT(H, ldh, k, k - 1) = 0.0;
             best = fmax(best, (double)k);
         }
     }
-    return (int)block_reduce(best, true);
+    return (int)block_reduce<BT>(best, true);
 }
 
-// C (w x len, in HBM) <- U^T C, U (w x w) in LDS with leading dimension ldu.
-// Each 64-column tile of C is staged in LDS (stage: (wp+1) * 64 doubles).
-__device__ __forceinline__ void wg_update_left(double *C, int ldc, int w, int len, const double *U, int ldu, double *stage) {
-    if (len <= 0 || w <= 0) return;
-    const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
-    const int li = lane & 15, lk = lane >> 4;
-    const int wp = (w + 15) & ~15, kp = (w + 3) & ~3, nrt = wp >> 4;
-    const int lds = wp + 1;
-    for (int c0 = 0; c0 < len; c0 += 64) {
-        for (int idx = threadIdx.x; idx < wp * 64; idx += NT) {
-            const int r = idx % wp, c = idx / wp;
-            stage[r + c * lds] = (r < w && c0 + c < len) ? AT(C, ldc, r, c0 + c) : 0.0;
+// Sixteen vectors of length w (NTL = ceil(w / 16)) times U, in place, by one wave:
+// x_i <- U^T x_i, entry k of vector i at C[i * si + k * sk].  Columns of H (si = ldh,
+// sk = 1) or rows of H and Z (si = 1, sk = ld: then lanes read and write runs of 16
+// entries); vectors from len on are left alone.  U in LDS.
+template <int NTL>
+__device__ __forceinline__ void wave_update(double *C, size_t sk, size_t si, int len, int w, const double *U, int ldu) {
+    const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+    const bool on = li < len;
+    typedef __attribute__((address_space(1))) double global_double;  // also after the asm below
+    global_double *const p = (global_double *)(C + (on ? li : 0) * si + lk * sk), *q = p;
+    double b[4 * NTL];
+#pragma unroll
+    for (int s = 0; s < 4 * NTL; ++s, q += 4 * sk) {
+        // entries past the end (in the last tile) count as zeros
+        if (s < 4 * (NTL - 1)) {
+            b[s] = *q;
+        } else {
+            b[s] = 0.0;
+            if (4 * s + lk < w) b[s] = *q;
         }
-        __syncthreads();
-        neig_d4 acc[6];
+    }
+    neig_d4 acc[NTL];
+    int col[NTL];
 #pragma unroll
-        for (int t = 0; t < 6; ++t) acc[t] = (neig_d4){0.0, 0.0, 0.0, 0.0};
-        const int cb = 16 * q + li;
-        for (int k = 0; k < kp; k += 4) {
-            const int kk = k + lk;
-            const double b = stage[kk + cb * lds];
-#pragma unroll
-            for (int rt = 0; rt < 6; ++rt) {
-                if (rt < nrt) {
-                    const int ar = 16 * rt + li;
-                    const double a = (ar < w && kk < w) ? U[kk + ar * ldu] : 0.0;
-                    acc[rt] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc[rt], 0, 0, 0);
-                }
-            }
+    for (int t = 0; t < NTL; ++t) {
+        acc[t] = (neig_d4){0.0, 0.0, 0.0, 0.0};
+        const int c = 16 * t + li;
+        col[t] = ((t < NTL - 1) ? c : min(c, w - 1)) * ldu;
+    }
+    double a[NTL];
+    auto fetch = [&](int s) __attribute__((always_inline)) {
+        int k = 4 * s + lk;
+        if (s >= 4 * (NTL - 1)) {
+            k = min(k, w - 1);
+            asm volatile("" : "+v"(k));  // computed here, not kept for the next tile
         }
-        const int col = c0 + cb;
-        if (col < len) {
 #pragma unroll
-            for (int rt = 0; rt < 6; ++rt) {
-                if (rt < nrt) {
+        for (int t = 0; t < NTL; ++t) a[t] = U[k + col[t]];
+    };
+    fetch(0);
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int row = 16 * rt + lk + 4 * r;
-                        if (row < w) AT(C, ldc, row, col) = acc[rt][r];
-                    }
-                }
-            }
-        }
-        __syncthreads();
+    for (int s = 0; s < 4 * NTL; ++s) {
+        double f[NTL];
+#pragma unroll
+        for (int t = 0; t < NTL; ++t) f[t] = a[t];
+        // one column of U is read ahead and no more: reads of all of them first would
+        // not fit the registers
+        if (s + 1 < 4 * NTL) fetch(s + 1);
+#pragma unroll
+        for (int t = 0; t < NTL; ++t) acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(f[t], b[s], acc[t], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    q = p;
+    asm volatile("" : "+v"(q));  // the loads' addresses are not kept for the stores
+    if (on) {
+#pragma unroll
+        for (int s = 0; s < 4 * NTL; ++s, q += 4 * sk)
+            if (s < 4 * (NTL - 1) || 4 * s + lk < w) *q = acc[s / 4][s % 4];
     }
 }
 
-// C (len x w, in HBM) <- C U, U (w x w) in LDS.
-__device__ __forceinline__ void wg_update_right(double *C, int ldc, int len, int w, const double *U, int ldu) {
-    if (len <= 0 || w <= 0) return;
-    const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
-    const int li = lane & 15, lk = lane >> 4;
-    const int wp = (w + 15) & ~15, kp = (w + 3) & ~3, nct = wp >> 4;
-    for (int r0 = 0; r0 < len; r0 += 64) {
-        const int rbase = r0 + 16 * q;
-        const int arow = rbase + li;
-        neig_d4 acc[6];
-#pragma unroll
-        for (int t = 0; t < 6; ++t) acc[t] = (neig_d4){0.0, 0.0, 0.0, 0.0};
-        for (int k = 0; k < kp; k += 4) {
-            const int kk = k + lk;
-            const double a = (arow < len && kk < w) ? AT(C, ldc, arow, kk) : 0.0;
-#pragma unroll
-            for (int ct = 0; ct < 6; ++ct) {
-                if (ct < nct) {
-                    const int bc = 16 * ct + li;
-                    const double b = (bc < w && kk < w) ? U[kk + bc * ldu] : 0.0;
-                    acc[ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc[ct], 0, 0, 0);
-                }
-            }
+// The rest of H and Z after rows and columns lo..lo+w-1 were transformed by U (w x w,
+// in LDS): columns right..n-1 and rows 0..above-1 of H, all rows of Z.  The vectors
+// are shared out to the waves sixteen at a time, without a barrier (they are
+// disjoint); ends with one.
+template <int NTL>
+__device__ __forceinline__ void wg_update_tiles(double *H, int ldh, double *Z, int ldz, int n, int lo, int w, int above,
+                                                int right, const double *U, int ldu) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int tl = (n - right + 15) >> 4, ta = (above + 15) >> 4, tz = (n + 15) >> 4;
+#pragma unroll 1
+    for (int t = wave; t < tl + ta + tz; t += BT / 64) {
+        double *C;
+        size_t sk, si;
+        int len;
+        if (t < tl) {
+            const int c = right + 16 * t;
+            C = H + lo + (size_t)c * ldh;
+            sk = 1;
+            si = ldh;
+            len = n - c;
+        } else {
+            const bool inH = t < tl + ta;
+            const int r = 16 * (t - tl - (inH ? 0 : ta));
+            C = (inH ? H : Z) + r + (size_t)lo * (inH ? ldh : ldz);
+            sk = inH ? ldh : ldz;
+            si = 1;
+            len = (inH ? above : n) - r;
         }
-#pragma unroll
-        for (int ct = 0; ct < 6; ++ct) {
-            if (ct < nct) {
-                const int col = 16 * ct + li;
-                if (col < w) {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int row = rbase + lk + 4 * r;
-                        if (row < len) AT(C, ldc, row, col) = acc[ct][r];
-                    }
-                }
-            }
-        }
+        wave_update<NTL>(C, sk, si, len, w, U, ldu);
+    }
+}
+
+// ---------------------------------------------------------------- phases
+//
+// The phases are functions of their own (not inlined): each then has the 168
+// registers of a lane to itself, where in one body the compiler kept values of all
+// phases alive and spilled in the innermost loops (the window QR 14% slower).  Their
+// arguments arrive in vector registers; uni() makes them uniform again.  All
+// BT threads call, after a barrier; all end with one.
+
+__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ double uni(double v) {
+    return __hiloint2double(uni(__double2hiint(v)), uni(__double2loint(v)));
+}
+__device__ __forceinline__ double *uni(double *p) {
+    const unsigned long long v = (unsigned long long)p;
+    const unsigned long long u = ((unsigned long long)(unsigned)uni((int)(v >> 32)) << 32) | (unsigned)uni((int)v);
+    return (double *)(__attribute__((address_space(1))) double *)u;  // global memory, not LDS
+}
+
+// The rest of H and Z after rows and columns lo..lo+w-1 were transformed by the
+// w x w matrix at lds + uoff.
+__device__ __attribute__((noinline)) void b_update(double *H, int ldh, double *Z, int ldz, int n, int lo, int w, int above,
+                                                   int right, int uoff, int ldu) {
+    extern __shared__ double lds[];
+    static_assert(NEIG_CHASE_MAX <= 96 && NEIG_SMALL_MAX <= 96, "six row tiles");
+    H = uni(H); ldh = uni(ldh); Z = uni(Z); ldz = uni(ldz); n = uni(n); lo = uni(lo); w = uni(w);
+    above = uni(above); right = uni(right); ldu = uni(ldu);
+    const double *U = lds + uni(uoff);
+    switch ((w + 15) >> 4) {
+    case 1: wg_update_tiles<1>(H, ldh, Z, ldz, n, lo, w, above, right, U, ldu); break;
+    case 2: wg_update_tiles<2>(H, ldh, Z, ldz, n, lo, w, above, right, U, ldu); break;
+    case 3: wg_update_tiles<3>(H, ldh, Z, ldz, n, lo, w, above, right, U, ldu); break;
+    case 4: wg_update_tiles<4>(H, ldh, Z, ldz, n, lo, w, above, right, U, ldu); break;
+    case 5: wg_update_tiles<5>(H, ldh, Z, ldz, n, lo, w, above, right, U, ldu); break;
+    default: wg_update_tiles<6>(H, ldh, Z, ldz, n, lo, w, above, right, U, ldu); break;
     }
     __syncthreads();
 }
 
-// The rest of H and Z after the diagonal block [lo, hi] was transformed by U.
-__device__ __forceinline__ void wg_block_updates(double *H, int ldh, double *Z, int ldz, int n, int lo, int hi, const double *U,
-                                 int ldu, double *stage) {
-    const int w = hi - lo + 1;
-    wg_update_left(H + lo + (size_t)(hi + 1) * ldh, ldh, w, n - hi - 1, U, ldu, stage);
-    wg_update_right(H + (size_t)lo * ldh, ldh, lo, w, U, ldu);
-    wg_update_right(Z + (size_t)lo * ldz, ldz, n, w, U, ldu);
+// The m x m diagonal block of H at off into LDS and its Schur form there, its factor
+// behind it (leading dimensions m + 1); what lds_small_qr returns.
+__device__ __attribute__((noinline)) int b_qr(const double *H, int ldh, int off, int m, double hnorm, double smlnum) {
+    extern __shared__ double lds[];
+    H = uni((double *)H); ldh = uni(ldh); off = uni(off); m = uni(m); hnorm = uni(hnorm); smlnum = uni(smlnum);
+    const int ld = m + 1;
+    double *Q = lds + (size_t)m * ld;
+    lds_load_block<BT>(H, ldh, off, m, lds, ld, Q, ld);
+    int iters = 0;
+    return lds_small_qr(lds, ld, Q, ld, m, hnorm, smlnum, 30 * (m > 10 ? m : 10), &iters);
 }
 
-// Staging space for left updates of width w: reuse `a` if it is large enough.
-__device__ __forceinline__ double *pick_stage(double *a, size_t a_len, double *spare, int w) {
-    const size_t need = (size_t)(((w + 15) & ~15) + 1) * 64;
-    return (a_len >= need) ? a : spare;
+// Write the m x m block in LDS back to H's diagonal block at off.
+__device__ __forceinline__ void b_store(double *H, int ldh, int off, int m) {
+    extern __shared__ double lds[];
+    for (int idx = threadIdx.x; idx < m * m; idx += BT) {
+        const int i = idx % m, j = idx / m;
+        AT(H, ldh, off + i, off + j) = (i <= j + 1) ? AT(lds, m + 1, i, j) : 0.0;
+    }
 }
 
-// ---------------------------------------------------------------- one chase window (NT threads)
+// The deflation half of the AED step on the window in LDS (infqr: b_qr's result); the
+// window back to H if anything deflated, the Ritz values to sr, si and their number to
+// *nritz (all in LDS).  Returns the number of deflated rows.
+__device__ __attribute__((noinline)) int b_deflate(double *H, int ldh, int ktop, int kwtop, int nw, int infqr, double s,
+                                                   double hnorm, double smlnum, int criterion) {
+    extern __shared__ double lds[];
+    H = uni(H); ldh = uni(ldh); ktop = uni(ktop); kwtop = uni(kwtop); nw = uni(nw); infqr = uni(infqr);
+    s = uni(s); hnorm = uni(hnorm); smlnum = uni(smlnum); criterion = uni(criterion);
+    BShifts &b = batch_shifts();
+    const int ld = nw + 1;
+    double *V = lds + (size_t)nw * ld;
+    AedOut o;
+    o.infqr = infqr;
+    aed_deflate<BT>(lds, V, ld, V + (size_t)nw * ld, nw, s, hnorm, smlnum, criterion, b.rr, b.ri, o);
+    if (o.nd > 0) {
+        b_store(H, ldh, kwtop, nw);
+        if (kwtop > ktop && threadIdx.x == 0) AT(H, ldh, kwtop, kwtop - 1) = o.spike0;
+    }
+    if (threadIdx.x == 0) b.nritz = o.nritz;
+    __syncthreads();
+    return o.nd;
+}
 
-// Chase bulges b = 0..nb-1 (polynomial pairs in ptr/pdet) through steps t0..t1-1
-// of the window r0..r1 of the active block ktop..kbot; the window (rows and
-// columns b0..r1) and its accumulated factor U live in LDS.
-__device__ __forceinline__ void wg_chase_window(double *H, int ldh, int ktop, int kbot, int r0, int r1, int t0, int t1, int nb,
-                                const double *ptr, const double *pdet, double *Hs, double *Us) {
-    __shared__ double rtau[B_MAX_BULGES], rv1[B_MAX_BULGES], rv2[B_MAX_BULGES];
-    __shared__ int rpos[B_MAX_BULGES], rm3[B_MAX_BULGES];
-    const int tid = threadIdx.x;
-    const int b0 = (r0 > 0) ? r0 - 1 : 0;
-    const int mb = r1 - b0 + 1, w = r1 - r0 + 1;
-    const int ldhs = mb + 1, ldus = w + 1;
-    for (int idx = tid; idx < mb * mb; idx += NT) {
-        const int i = idx % mb, j = idx / mb;
-        AT(Hs, ldhs, i, j) = AT(H, ldh, b0 + i, b0 + j);
-    }
-    for (int idx = tid; idx < w * w; idx += NT) {
-        const int i = idx % w, j = idx / w;
-        AT(Us, ldus, i, j) = (i == j) ? 1.0 : 0.0;
-    }
-    __syncthreads();
-    for (int t = t0; t < t1; ++t) {
-        if (tid < B_MAX_BULGES) {
-            const int b = tid;
-            const int pos = ktop + t - 3 * b;
-            if (b < nb && pos >= ktop && pos <= kbot - 1) {
-                const int m3 = (pos <= kbot - 2) ? 3 : 2;
-                const int p = pos - b0;
-                double x0, x1, x2;
-                if (pos == ktop) {
-                    const double h00 = AT(Hs, ldhs, p, p), h01 = AT(Hs, ldhs, p, p + 1);
-                    const double h10 = AT(Hs, ldhs, p + 1, p), h11 = AT(Hs, ldhs, p + 1, p + 1);
-                    const double h21 = (m3 == 3) ? AT(Hs, ldhs, p + 2, p + 1) : 0.0;
-                    const double tr = ptr[b], det = pdet[b];
-                    double sc = fmax(fmax(fabs(h00), fabs(h01)), fmax(fmax(fabs(h10), fabs(h11)), fabs(h21)));
-                    sc = fmax(sc, fmax(fabs(tr), sqrt(fabs(det))));
-                    if (sc == 0.0) sc = 1.0;
-                    const double rs = 1.0 / sc;
-                    const double aa = h00 * rs, bb = h01 * rs, cc = h10 * rs, dd = h11 * rs, ee = h21 * rs;
-                    const double tt = tr * rs, dt = det * rs * rs;
-                    x0 = aa * aa + bb * cc - tt * aa + dt;
-                    x1 = cc * (aa + dd - tt);
-                    x2 = cc * ee;
-                } else {
-                    x0 = AT(Hs, ldhs, p, p - 1);
-                    x1 = AT(Hs, ldhs, p + 1, p - 1);
-                    x2 = (m3 == 3) ? AT(Hs, ldhs, p + 2, p - 1) : 0.0;
-                }
-                const Refl r = make_refl(x0, x1, x2);
-                rtau[b] = r.tau; rv1[b] = r.v1; rv2[b] = (m3 == 3) ? r.v2 : 0.0;
-                rpos[b] = pos; rm3[b] = m3;
-                if (pos > ktop) {
-                    AT(Hs, ldhs, p, p - 1) = r.beta;
-                    AT(Hs, ldhs, p + 1, p - 1) = 0.0;
-                    if (m3 == 3) AT(Hs, ldhs, p + 2, p - 1) = 0.0;
-                }
-            } else {
-                rpos[b] = -1;
-                rtau[b] = 0.0;
-            }
-        }
-        __syncthreads();
-        // left: thread (column, bulge half) handles bulges g, g+2, ... in groups of 4
-        {
-            const int jl = tid & 127, g = tid >> 7;
-            if (jl < mb) {
-                const int j = b0 + jl;
-                for (int q0 = 0; q0 < B_MAX_BULGES / 2; q0 += 4) {
-                    double x[4][3];
-                    bool act[4];
-                    int pp[4];
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int b = g + 2 * (q0 + q);
-                        const int pos = (b < nb) ? rpos[b] : -1;
-                        act[q] = pos >= 0 && pos <= j;
-                        pp[q] = pos - b0;
-                        if (act[q]) {
-                            x[q][0] = AT(Hs, ldhs, pp[q], jl);
-                            x[q][1] = AT(Hs, ldhs, pp[q] + 1, jl);
-                            x[q][2] = (rm3[b] == 3) ? AT(Hs, ldhs, pp[q] + 2, jl) : 0.0;
-                        }
-                    }
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        if (!act[q]) continue;
-                        const int b = g + 2 * (q0 + q);
-                        const double tau = rtau[b], v1 = rv1[b], v2 = rv2[b];
-                        const double sv = tau * (x[q][0] + v1 * x[q][1] + v2 * x[q][2]);
-                        AT(Hs, ldhs, pp[q], jl) = x[q][0] - sv;
-                        AT(Hs, ldhs, pp[q] + 1, jl) = x[q][1] - sv * v1;
-                        if (rm3[b] == 3) AT(Hs, ldhs, pp[q] + 2, jl) = x[q][2] - sv * v2;
-                    }
-                }
-            }
-        }
-        __syncthreads();
-        // right: thread per row slot (H rows, then U rows), bulges in groups of 4
-        {
-            const bool isH = tid < 128;
-            const int il = isH ? tid : tid - 128;
-            if (isH ? (il < mb) : (il < w)) {
-                double *M = isH ? Hs : Us;
-                const int ldm = isH ? ldhs : ldus;
-                const int cbase = isH ? b0 : r0;
-                const int gi = b0 + il;
-                for (int b0g = 0; b0g < B_MAX_BULGES; b0g += 4) {
-                    double x[4][3];
-                    bool act[4];
-                    int pc[4];
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int b = b0g + q;
-                        const int pos = (b < nb) ? rpos[b] : -1;
-                        bool a = pos >= 0;
-                        if (a && isH) a = gi <= ((pos + 3 < kbot) ? pos + 3 : kbot);
-                        act[q] = a;
-                        pc[q] = pos - cbase;
-                        if (a) {
-                            x[q][0] = AT(M, ldm, il, pc[q]);
-                            x[q][1] = AT(M, ldm, il, pc[q] + 1);
-                            x[q][2] = (rm3[b] == 3) ? AT(M, ldm, il, pc[q] + 2) : 0.0;
-                        }
-                    }
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        if (!act[q]) continue;
-                        const int b = b0g + q;
-                        const double tau = rtau[b], v1 = rv1[b], v2 = rv2[b];
-                        const double sv = tau * (x[q][0] + v1 * x[q][1] + v2 * x[q][2]);
-                        AT(M, ldm, il, pc[q]) = x[q][0] - sv;
-                        AT(M, ldm, il, pc[q] + 1) = x[q][1] - sv * v1;
-                        if (rm3[b] == 3) AT(M, ldm, il, pc[q] + 2) = x[q][2] - sv * v2;
-                    }
-                }
-            }
-        }
-        __syncthreads();
-    }
-    // write back the changed part: columns r0..r1 (rows b0..r1) and column b0 below r0
-    const int off = r0 - b0;
-    for (int idx = tid; idx < mb * (mb - off); idx += NT) {
-        const int il = idx % mb, jl = off + idx / mb;
-        AT(H, ldh, b0 + il, b0 + jl) = AT(Hs, ldhs, il, jl);
-    }
-    if (off == 1 && r0 > ktop && tid < 3 && tid + 1 < mb) AT(H, ldh, r0 + tid, b0) = AT(Hs, ldhs, 1 + tid, 0);
-    __syncthreads();
+// One window of a sweep; its factor stays in LDS behind the window.
+__device__ __attribute__((noinline)) void b_chase(double *H, int ldh, int ktop, int kbot, int r0, int r1, int t0, int t1,
+                                                  int nb, int bulge0) {
+    extern __shared__ double lds[];
+    H = uni(H); ldh = uni(ldh); ktop = uni(ktop); kbot = uni(kbot);
+    ChaseWin W;
+    W.r0 = uni(r0); W.r1 = uni(r1); W.t0 = uni(t0); W.t1 = uni(t1); W.nb = uni(nb);
+    W.chain = 0;
+    const int mb = W.r1 - ((W.r0 > 0) ? W.r0 - 1 : 0) + 1;
+    chase_window(H, ldh, W, ktop, kbot, batch_shifts().poly + 2 * uni(bulge0), lds, lds + (size_t)mb * (mb | 1));
 }
 
 // ---------------------------------------------------------------- shifts (thread 0)
@@ -403,10 +367,8 @@ __device__ __forceinline__ int pick_shifts_dev(const double *rr, const double *r
 // formulas as the single-matrix path's neig_stats.alg_flops: 10 m^3 per window
 // or small block solved in LDS, 2 m^2 per row or column its factor is applied
 // to, 20 n per bulge position of a sweep); every thread holds the same value.
-__device__ __forceinline__ int solve_one(const BProb &P, const BTune &tu, const BArgs &A, double *lds, double *flops) {
-    __shared__ double s_rr[NEIG_SMALL_MAX], s_ri[NEIG_SMALL_MAX];
-    __shared__ double s_ptr[B_MAX_BULGES * 4], s_pdet[B_MAX_BULGES * 4];
-    __shared__ int s_nsh;
+__device__ __forceinline__ int solve_one(const BProb &P, const BTune &tu, const BArgs &A, double *flops) {
+    BShifts &sh = batch_shifts();
     const int tid = threadIdx.x;
     const int n = P.n;
     double *H = P.H, *Z = P.Z;
@@ -425,19 +387,9 @@ __device__ __forceinline__ int solve_one(const BProb &P, const BTune &tu, const 
         const int m = kbot - ktop + 1;
         if (m <= nmin) {
             if (m > 1) {  // whole block in LDS, then its factor to the rest
-                const int ld = m + 1;
-                double *T = lds, *Q = lds + (size_t)m * ld;
-                lds_load_block(H, ldh, ktop, m, T, ld, Q, ld);
-                int iters = 0;
-                const int bad = lds_small_qr(T, ld, Q, ld, m, hnorm, smlnum, 30 * (m > 10 ? m : 10), &iters);
-                __syncthreads();
-                for (int idx = tid; idx < m * m; idx += NT) {
-                    const int i = idx % m, j = idx / m;
-                    AT(H, ldh, ktop + i, ktop + j) = (i <= j + 1) ? AT(T, ld, i, j) : 0.0;
-                }
-                __syncthreads();
-                double *stage = pick_stage(T, (size_t)m * ld, Q + (size_t)m * ld, m);
-                wg_block_updates(H, ldh, Z, ldz, n, ktop, kbot, Q, ld, stage);
+                const int bad = uni(b_qr(H, ldh, ktop, m, hnorm, smlnum));
+                b_store(H, ldh, ktop, m);
+                b_update(H, ldh, Z, ldz, n, ktop, m, ktop, kbot + 1, m * (m + 1), m + 1);
                 fl += 10.0 * m * (double)m * m + 2.0 * m * (double)m * (ktop + (n - kbot - 1) + n);
                 if (bad > 0) {
                     info = ktop + bad;
@@ -455,30 +407,19 @@ __device__ __forceinline__ int solve_one(const BProb &P, const BTune &tu, const 
         // AED on the trailing window
         int nw = tu.nw < m ? tu.nw : m;
         const int kwtop = kbot - nw + 1;
-        const int ld = nw + 1;
-        double *T = lds, *V = lds + (size_t)nw * ld, *x = V + (size_t)nw * ld;
-        const double s = (kwtop > ktop) ? AT(H, ldh, kwtop, kwtop - 1) : 0.0;
-        __syncthreads();
-        lds_load_block(H, ldh, kwtop, nw, T, ld, V, ld);
-        const AedOut o = aed_core(T, V, ld, x, nw, s, hnorm, smlnum, A.criterion, 30 * (nw > 10 ? nw : 10), s_rr,
-                                  s_ri);
+        const double spike = (kwtop > ktop) ? AT(H, ldh, kwtop, kwtop - 1) : 0.0;
+        const int infqr = uni(b_qr(H, ldh, kwtop, nw, hnorm, smlnum));
+        const int nd = uni(b_deflate(H, ldh, ktop, kwtop, nw, infqr, spike, hnorm, smlnum, A.criterion));
         fl += 10.0 * nw * (double)nw * nw;
-        if (o.nd > 0) fl += 2.0 * nw * (double)nw * (kwtop + (n - kbot - 1) + n);
-        if (o.nd > 0) {
-            for (int idx = tid; idx < nw * nw; idx += NT) {
-                const int i = idx % nw, j = idx / nw;
-                AT(H, ldh, kwtop + i, kwtop + j) = (i <= j + 1) ? AT(T, ld, i, j) : 0.0;
-            }
-            if (kwtop > ktop && tid == 0) AT(H, ldh, kwtop, kwtop - 1) = o.spike0;
-            __syncthreads();
-            double *stage = pick_stage(T, (size_t)nw * ld, x + nw, nw);
-            wg_block_updates(H, ldh, Z, ldz, n, kwtop, kbot, V, ld, stage);
+        if (nd > 0) {
+            fl += 2.0 * nw * (double)nw * (kwtop + (n - kbot - 1) + n);
+            b_update(H, ldh, Z, ldz, n, kwtop, nw, kwtop, kbot + 1, nw * (nw + 1), nw + 1);
         }
-        kbot -= o.nd;
-        ndefl = (o.nd > 0) ? 0 : ndefl + 1;
+        kbot -= nd;
+        ndefl = (nd > 0) ? 0 : ndefl + 1;
         const int m2 = kbot - ktop + 1;
         if (m2 <= nmin) continue;
-        if (o.nd > 0 && 100 * o.nd > A.nibble * nw) continue;
+        if (nd > 0 && 100 * nd > A.nibble * nw) continue;
         // shifts
         int ns = tu.ns;
         if (ns > 2 * B_MAX_BULGES) ns = 2 * B_MAX_BULGES;
@@ -498,7 +439,7 @@ __device__ __forceinline__ int solve_one(const BProb &P, const BTune &tu, const 
                     got += 2;
                 }
             } else {
-                got = pick_shifts_dev(s_rr, s_ri, o.nritz, ns, xr, xi);
+                got = pick_shifts_dev(sh.rr, sh.ri, sh.nritz, ns, xr, xi);
             }
             if (got < 2) {
                 const double a = AT(H, ldh, kbot - 1, kbot - 1), b = AT(H, ldh, kbot - 1, kbot);
@@ -513,18 +454,18 @@ __device__ __forceinline__ int solve_one(const BProb &P, const BTune &tu, const 
                 got = 2;
             }
             for (int g = 0; g < got / 2; ++g) {
-                s_ptr[g] = xr[2 * g] + xr[2 * g + 1];
-                s_pdet[g] = xr[2 * g] * xr[2 * g + 1] - xi[2 * g] * xi[2 * g + 1];
+                sh.poly[2 * g] = xr[2 * g] + xr[2 * g + 1];
+                sh.poly[2 * g + 1] = xr[2 * g] * xr[2 * g + 1] - xi[2 * g] * xi[2 * g + 1];
             }
-            s_nsh = got;
+            sh.nsh = got;
         }
         __syncthreads();
-        // sweep: chains of at most B_MAX_BULGES bulges, one after another
-        const int nbulge = s_nsh / 2;
+        // sweep: chains of at most CHASE_MAX_BULGES bulges, one after another
+        const int nbulge = uni(sh.nsh) / 2;
         const int wmax = tu.wchase;
         fl += 20.0 * n * (double)nbulge * (kbot - ktop);
-        for (int c0 = 0; c0 < nbulge; c0 += B_MAX_BULGES) {
-            const int nb = (nbulge - c0 < B_MAX_BULGES) ? nbulge - c0 : B_MAX_BULGES;
+        for (int c0 = 0; c0 < nbulge; c0 += CHASE_MAX_BULGES) {
+            const int nb = (nbulge - c0 < CHASE_MAX_BULGES) ? nbulge - c0 : CHASE_MAX_BULGES;
             const int tend = kbot - 1 - ktop + 3 * (nb - 1);
             int t = 0;
             while (t <= tend) {
@@ -533,12 +474,8 @@ __device__ __forceinline__ int solve_one(const BProb &P, const BTune &tu, const 
                 const int t1 = (r1 < kbot) ? r1 - 3 - ktop + 1 : tend + 1;
                 const int b0 = (r0 > 0) ? r0 - 1 : 0;
                 const int mb = r1 - b0 + 1, w = r1 - r0 + 1;
-                double *Hs = lds, *Us = lds + (size_t)mb * (mb + 1);
-                wg_chase_window(H, ldh, ktop, kbot, r0, r1, t, t1, nb, s_ptr + c0, s_pdet + c0, Hs, Us);
-                double *stage = pick_stage(Hs, (size_t)mb * (mb + 1), Us + (size_t)w * (w + 1), w);
-                wg_update_left(H + r0 + (size_t)(r1 + 1) * ldh, ldh, w, n - r1 - 1, Us, w + 1, stage);
-                wg_update_right(H + (size_t)r0 * ldh, ldh, b0, w, Us, w + 1);
-                wg_update_right(Z + (size_t)r0 * ldz, ldz, n, w, Us, w + 1);
+                b_chase(H, ldh, ktop, kbot, r0, r1, t, t1, nb, c0);
+                b_update(H, ldh, Z, ldz, n, r0, w, b0, r1 + 1, mb * (mb | 1), w | 1);
                 t = t1;
             }
         }
@@ -546,14 +483,14 @@ __device__ __forceinline__ int solve_one(const BProb &P, const BTune &tu, const 
     // standardise any decoupled 2x2 block not yet in standard form, then (wr, wi)
     __syncthreads();
     double nflag = 0.0;
-    for (int j = tid; j + 1 < n; j += NT) {
+    for (int j = tid; j + 1 < n; j += BT) {
         const double c = AT(H, ldh, j + 1, j);
         if (c == 0.0) continue;
         if (j > 0 && AT(H, ldh, j, j - 1) != 0.0) continue;
         if (j + 2 < n && AT(H, ldh, j + 2, j + 1) != 0.0) continue;
         if (!(AT(H, ldh, j, j) == AT(H, ldh, j + 1, j + 1) && AT(H, ldh, j, j + 1) * c < 0.0)) nflag += 1.0;
     }
-    nflag = block_reduce(nflag, false);
+    nflag = block_reduce<BT>(nflag, false);
     for (int j = 0; nflag > 0.0 && j + 1 < n; ++j) {
         const double c = AT(H, ldh, j + 1, j);
         if (c == 0.0) continue;
@@ -563,7 +500,7 @@ __device__ __forceinline__ int solve_one(const BProb &P, const BTune &tu, const 
         if (a == d && b * c < 0.0) continue;
         const Std2 o = std2x2(a, b, c, d);
         __syncthreads();
-        for (int idx = tid; idx < n; idx += NT) {
+        for (int idx = tid; idx < n; idx += BT) {
             if (idx >= j + 2) {
                 const double xx = AT(H, ldh, j, idx), yy = AT(H, ldh, j + 1, idx);
                 AT(H, ldh, j, idx) = o.cs * xx + o.sn * yy;
@@ -584,7 +521,7 @@ __device__ __forceinline__ int solve_one(const BProb &P, const BTune &tu, const 
         }
         __syncthreads();
     }
-    for (int j = tid; j < n; j += NT) {
+    for (int j = tid; j < n; j += BT) {
         const bool starts = (j + 1 < n) && AT(H, ldh, j + 1, j) != 0.0;
         const bool ends = (j > 0) && AT(H, ldh, j, j - 1) != 0.0;
         if (starts && !ends) {
@@ -603,8 +540,7 @@ __device__ __forceinline__ int solve_one(const BProb &P, const BTune &tu, const 
     return info;
 }
 
-extern "C" __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1))) k_batched(BArgs A) {
-    extern __shared__ double lds[];
+extern "C" __global__ void __launch_bounds__(BT) k_batched(BArgs A) {
     __shared__ int s_idx;
     for (;;) {
         if (threadIdx.x == 0) s_idx = atomicAdd(A.next, 1);
@@ -618,7 +554,7 @@ extern "C" __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per
         int b = 0;
         while (b + 1 < B_NBUCKET && P.n > A.bucket_hi[b]) ++b;
         double fl = 0.0;
-        const int info = solve_one(P, A.tune[b], A, lds, &fl);
+        const int info = solve_one(P, A.tune[b], A, &fl);
         if (threadIdx.x == 0) {
             A.info[p] = info;
             atomicAdd((double *)(A.next + 2), fl);

@@ -322,22 +322,19 @@ __device__ __forceinline__ void chase_far_rows(double *Hs, int ldhs, int mb, dou
     }
 }
 
-extern "C" __global__ void __launch_bounds__(CHASE_THREADS)
-k_chase(double *H, int ldh, const double *poly, double *Ut, ChaseArgs a) {
-    extern __shared__ double lds[];
+// One window by CHASE_THREADS threads: load, chase, write the window back to H.
+// Hs and Us take mb and w columns of odd length; U stays in Us (leading dimension
+// w | 1); ends with a barrier.
+__device__ __forceinline__ void chase_window(double *H, int ldh, const ChaseWin &W, int ktop, int kbot,
+                                             const double *poly, double *Hs, double *Us) {
     __shared__ double cq[2][CHASE_BATCH][CHASE_MAX_BULGES][4];  // two batches' reflectors (q, u0, u1, u2)
-    const ChaseWin W = a.win[blockIdx.x];
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int ktop = a.ktop, kbot = a.kbot;
     const int r0 = W.r0, r1 = W.r1;
     const int b0 = (r0 > 0) ? r0 - 1 : 0;
     const int mb = r1 - b0 + 1;  // LDS block order
     const int w = r1 - r0 + 1;   // U order
     const int ldhs = mb | 1, ldus = w | 1;
-    double *Hs = lds;
-    double *Us = lds + (size_t)mb * ldhs;
-    const double *mypoly = poly + 2 * (size_t)W.chain * a.nbc;
 
     for (int idx = tid; idx < mb * mb; idx += CHASE_THREADS) {
         const int i = idx % mb, j = idx / mb;
@@ -351,24 +348,34 @@ k_chase(double *H, int ldh, const double *poly, double *Ut, ChaseArgs a) {
     // both kinds of waves meet the same barriers: one before the first step, two
     // per step, one after the last
     if (wave < CHASE_NEAR) {
-        chase_near(Hs, ldhs, mb, b0, W, ktop, kbot, mypoly, cq, wave);
+        chase_near(Hs, ldhs, mb, b0, W, ktop, kbot, poly, cq, wave);
         __syncthreads();
     } else {
         chase_far_rows(Hs, ldhs, mb, Us, ldus, b0, W, ktop, cq, wave - CHASE_NEAR);
     }
     __syncthreads();
 
-    // write back what the window changed: columns r0..r1 (rows b0..r1), the three
-    // entries of column b0 below r0, and U^T
+    // write back what the window changed: columns r0..r1 (rows b0..r1) and the three
+    // entries of column b0 below r0
     const int off = r0 - b0;
     for (int idx = tid; idx < mb * (mb - off); idx += CHASE_THREADS) {
         const int il = idx % mb, jl = off + idx / mb;
         AT(H, ldh, b0 + il, b0 + jl) = AT(Hs, ldhs, il, jl);
     }
     if (off == 1 && r0 > ktop && tid < 3 && tid + 1 < mb) AT(H, ldh, r0 + tid, b0) = AT(Hs, ldhs, 1 + tid, 0);
+    __syncthreads();
+}
+
+extern "C" __global__ void __launch_bounds__(CHASE_THREADS)
+k_chase(double *H, int ldh, const double *poly, double *Ut, ChaseArgs a) {
+    extern __shared__ double lds[];
+    const ChaseWin W = a.win[blockIdx.x];
+    const int mb = W.r1 - ((W.r0 > 0) ? W.r0 - 1 : 0) + 1, w = W.r1 - W.r0 + 1;
+    double *Us = lds + (size_t)mb * (mb | 1);
+    chase_window(H, ldh, W, a.ktop, a.kbot, poly + 2 * (size_t)W.chain * a.nbc, lds, Us);
     double *Uo = Ut + (size_t)blockIdx.x * a.ldut * a.ldut;
-    for (int idx = tid; idx < w * w; idx += CHASE_THREADS) {
+    for (int idx = threadIdx.x; idx < w * w; idx += CHASE_THREADS) {
         const int r = idx % w, c = idx / w;
-        AT(Uo, a.ldut, r, c) = AT(Us, ldus, c, r);
+        AT(Uo, a.ldut, r, c) = AT(Us, w | 1, c, r);
     }
 }

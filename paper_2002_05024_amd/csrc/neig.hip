@@ -1678,7 +1678,7 @@ void launch_batched_pair(int batch, const int *n, double *const *H, const int *l
     const int grid = std::max(1, std::min(batch, cus > 0 ? cus : 256));
     const size_t lds = (size_t)(NEIG_CHASE_MAX + 1) * (NEIG_CHASE_MAX + 2) * sizeof(double) +
                        (size_t)NEIG_CHASE_MAX * (NEIG_CHASE_MAX + 1) * sizeof(double);
-    hipLaunchKernelGGL(k_batched, dim3(grid), dim3(NT), lds, stream, A);
+    hipLaunchKernelGGL(k_batched, dim3(grid), dim3(BT), lds, stream, A);
     ck(hipGetLastError());
 }
 

@@ -17,26 +17,28 @@
 #include "neig_dev.h"
 #include <climits>
 
-#define NT 256     // threads per workgroup
+#define NT 256     // threads per workgroup; the functions below take another count as NTH
 #define LANES 64   // wavefront size
 #define FB 15      // reflectors per batch handed to the accumulating waves
 
 // Block-wide max / sum (all NT threads call; result in every thread).
+template <int NTH = NT>
 __device__ __forceinline__ double block_reduce(double v, bool is_max) {
-    __shared__ double red[NT / LANES];
+    __shared__ double red[NTH / LANES];
     v = is_max ? wave_max(v) : wave_sum(v);
     __syncthreads();
     if ((threadIdx.x & (LANES - 1)) == 0) red[threadIdx.x / LANES] = v;
     __syncthreads();
     double r = red[0];
 #pragma unroll
-    for (int w = 1; w < NT / LANES; ++w) r = is_max ? fmax(r, red[w]) : r + red[w];
+    for (int w = 1; w < NTH / LANES; ++w) r = is_max ? fmax(r, red[w]) : r + red[w];
     return r;
 }
 
 // rows r, r+1 of M, columns c0..c1: (x, y) <- (cs x + sn y, -sn x + cs y)
+template <int NTH = NT>
 __device__ __forceinline__ void lds_rot_rows(double *M, int ld, int r, int c0, int c1, double cs, double sn) {
-    for (int j = c0 + (int)threadIdx.x; j <= c1; j += NT) {
+    for (int j = c0 + (int)threadIdx.x; j <= c1; j += NTH) {
         double x = AT(M, ld, r, j), y = AT(M, ld, r + 1, j);
         AT(M, ld, r, j) = cs * x + sn * y;
         AT(M, ld, r + 1, j) = -sn * x + cs * y;
@@ -44,8 +46,9 @@ __device__ __forceinline__ void lds_rot_rows(double *M, int ld, int r, int c0, i
 }
 
 // columns c, c+1 of M, rows r0..r1
+template <int NTH = NT>
 __device__ __forceinline__ void lds_rot_cols(double *M, int ld, int c, int r0, int r1, double cs, double sn) {
-    for (int i = r0 + (int)threadIdx.x; i <= r1; i += NT) {
+    for (int i = r0 + (int)threadIdx.x; i <= r1; i += NTH) {
         double x = AT(M, ld, i, c), y = AT(M, ld, i, c + 1);
         AT(M, ld, i, c) = cs * x + sn * y;
         AT(M, ld, i, c + 1) = -sn * x + cs * y;
@@ -54,13 +57,14 @@ __device__ __forceinline__ void lds_rot_cols(double *M, int ld, int c, int r0, i
 
 // Standardise the 2x2 block at (j, j) of the m x m matrix T (rotation applied to
 // whole rows and columns of T and to the columns of Q).
+template <int NTH = NT>
 __device__ __forceinline__ void lds_standardise(double *T, int ldt, double *Q, int ldq, int m, int j) {
     Std2 o = std2x2(AT(T, ldt, j, j), AT(T, ldt, j, j + 1), AT(T, ldt, j + 1, j), AT(T, ldt, j + 1, j + 1));
     __syncthreads();
     if (!(o.cs == 1.0 && o.sn == 0.0)) {
-        lds_rot_rows(T, ldt, j, j + 2, m - 1, o.cs, o.sn);
-        lds_rot_cols(T, ldt, j, 0, j - 1, o.cs, o.sn);
-        lds_rot_cols(Q, ldq, j, 0, m - 1, o.cs, o.sn);
+        lds_rot_rows<NTH>(T, ldt, j, j + 2, m - 1, o.cs, o.sn);
+        lds_rot_cols<NTH>(T, ldt, j, 0, j - 1, o.cs, o.sn);
+        lds_rot_cols<NTH>(Q, ldq, j, 0, m - 1, o.cs, o.sn);
     }
     if (threadIdx.x == 0) {
         AT(T, ldt, j, j) = o.a; AT(T, ldt, j, j + 1) = o.b;
@@ -686,8 +690,9 @@ __device__ __forceinline__ int lds_small_qr(double *T, int ldt, double *Q, int l
 
 // Load the m x m diagonal block of H at (off, off) into T (zeros below the
 // subdiagonal) and set Q = I.
+template <int NTH = NT>
 __device__ __forceinline__ void lds_load_block(const double *H, int ldh, int off, int m, double *T, int ldt, double *Q, int ldq) {
-    for (int idx = threadIdx.x; idx < m * m; idx += NT) {
+    for (int idx = threadIdx.x; idx < m * m; idx += NTH) {
         const int i = idx % m, j = idx / m;
         AT(T, ldt, i, j) = (i <= j + 1) ? AT(H, ldh, off + i, off + j) : 0.0;
         AT(Q, ldq, i, j) = (i == j) ? 1.0 : 0.0;
@@ -696,9 +701,10 @@ __device__ __forceinline__ void lds_load_block(const double *H, int ldh, int off
 }
 
 // Write T back to H's diagonal block and Q^T to Ut (column-major, ld ldut).
+template <int NTH = NT>
 __device__ __forceinline__ void lds_store(double *H, int ldh, int off, int m, const double *T, int ldt, const double *Q, int ldq,
                           double *Ut, int ldut) {
-    for (int idx = threadIdx.x; idx < m * m; idx += NT) {
+    for (int idx = threadIdx.x; idx < m * m; idx += NTH) {
         const int i = idx % m, j = idx / m;
         AT(H, ldh, off + i, off + j) = (i <= j + 1) ? AT(T, ldt, i, j) : 0.0;
         AT(Ut, ldut, i, j) = AT(Q, ldq, j, i);
@@ -1094,8 +1100,9 @@ __device__ __forceinline__ bool swap_transform(const double (&B)[P + Q][P + Q], 
 
 // Block starts of the quasi-triangular window T, no movers.  All NT threads
 // call, after a barrier; ends with one.
+template <int NTH = NT>
 __device__ __forceinline__ void swap_begin(SwapState &w, const double *T, int ld, int nw) {
-    for (int r = threadIdx.x; r <= nw; r += NT) {
+    for (int r = threadIdx.x; r <= nw; r += NTH) {
         w.head[r] = r == 0 || r == nw || AT(T, ld, r, r - 1) == 0.0;
         if (r < nw) w.mover[r] = 0;
     }
@@ -1178,10 +1185,11 @@ __device__ __forceinline__ void swap_apply(double *T, double *V, int ld, int nw,
     }
 }
 
+template <int NTH = NT>
 __device__ __forceinline__ void swap_apply_all(SwapState &w, double *T, double *V, int ld, int nw, int pairs,
                                                bool left) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / LANES);
-    for (int s = wave; s < pairs; s += NT / LANES) {
+    for (int s = wave; s < pairs; s += NTH / LANES) {
         const int st = __builtin_amdgcn_readfirstlane(w.st[s]), n = __builtin_amdgcn_readfirstlane(w.n[s]);
         if (st < 0) continue;
         if (n == 2) swap_apply<2>(T, V, ld, nw, st, w.q[s], left);
@@ -1193,8 +1201,9 @@ __device__ __forceinline__ void swap_apply_all(SwapState &w, double *T, double *
 // One round on rows top..kend-1: every mover swaps with the block above it if
 // that is not a mover.  Returns the number of pairs (0: nothing can move); all
 // NT threads call, after a barrier; ends with one.
+template <int NTH = NT>
 __device__ __forceinline__ int swap_round(SwapState &w, double *T, double *V, int ld, int nw, int top, int kend) {
-    for (int r = top + 1 + (int)threadIdx.x; r < kend; r += NT) {
+    for (int r = top + 1 + (int)threadIdx.x; r < kend; r += NTH) {
         if (!w.mover[r]) continue;
         const int a = w.head[r - 1] ? r - 1 : r - 2;
         if (a < top || w.mover[a]) continue;
@@ -1212,15 +1221,15 @@ __device__ __forceinline__ int swap_round(SwapState &w, double *T, double *V, in
     if (wave == 0) swap_transforms<1, 1>(w, 0, T, ld);
     else if (wave == 1) swap_transforms<1, 2>(w, 1, T, ld);
     else if (wave == 2) swap_transforms<2, 1>(w, 2, T, ld);
-    else swap_transforms<2, 2>(w, 3, T, ld);
+    else if (wave == 3) swap_transforms<2, 2>(w, 3, T, ld);
     __syncthreads();
-    swap_apply_all(w, T, V, ld, nw, pairs, true);
+    swap_apply_all<NTH>(w, T, V, ld, nw, pairs, true);
     if (threadIdx.x == 0) {
         w.total = 0;
         for (int t = 0; t < 4; ++t) w.cnt[t] = 0;
     }
     __syncthreads();
-    swap_apply_all(w, T, V, ld, nw, pairs, false);
+    swap_apply_all<NTH>(w, T, V, ld, nw, pairs, false);
     __syncthreads();
     // the 2x2 blocks of a swapped pair are similar to the old ones but not in
     // standard form; the caller standardises them once, after all swaps
@@ -1274,10 +1283,11 @@ __device__ __forceinline__ void win_house(G g, double *x, int len, double *tau, 
 // column or row and block-wide reductions before).
 
 // rows r0..r0+len-1 of M, columns c0..c1, from the left by I - tau v v^T
+template <int NTH = NT>
 __device__ __forceinline__ void win_refl_left(double *M, int ld, int r0, int len, int c0, int c1, double tau,
                                               const double *v) {
     const int part = threadIdx.x & 3;
-    for (int j0 = c0; j0 <= c1; j0 += NT / 4) {
+    for (int j0 = c0; j0 <= c1; j0 += NTH / 4) {
         const int j = j0 + (int)threadIdx.x / 4;
         const bool on = j <= c1;
         double *p = &AT(M, ld, r0, on ? j : c1);
@@ -1290,11 +1300,12 @@ __device__ __forceinline__ void win_refl_left(double *M, int ld, int r0, int len
 }
 
 // columns c0..c0+len-1 of M (rows 0..r1) and of M2 (rows 0..r2-1), from the right
+template <int NTH = NT>
 __device__ __forceinline__ void win_refl_right2(double *M, int ld, int r1, double *M2, int r2, int c0, int len,
                                                 double tau, const double *v) {
     const int part = threadIdx.x & 3;
     const int total = r1 + 1 + r2;
-    for (int i0 = 0; i0 < total; i0 += NT / 4) {
+    for (int i0 = 0; i0 < total; i0 += NTH / 4) {
         const int it = i0 + (int)threadIdx.x / 4;
         const bool on = it < total;
         const int i = on ? it : total - 1;
@@ -1356,6 +1367,7 @@ __device__ __forceinline__ bool aed_block_deflates(const double *T, const double
 // values, and the reduction of the spike and the undeflated part back to
 // Hessenberg form.  T, V and the vector scratch x (nw doubles) may be in LDS or
 // in global memory (generic pointers); all NT threads call.
+template <int NTH = NT>
 __device__ __forceinline__ void aed_deflate(double *T, double *V, int ld, double *x, int nw, double s, double hnorm,
                                             double smlnum, int criterion, double *sr, double *si, AedOut &o) {
     const int tid = threadIdx.x;
@@ -1364,7 +1376,7 @@ __device__ __forceinline__ void aed_deflate(double *T, double *V, int ld, double
     o.late = 0;
     o.swapfail = 0;
     SwapState &w = win_scratch().sw;
-    swap_begin(w, T, ld, nw);
+    swap_begin<NTH>(w, T, ld, nw);
     const int top = o.infqr;
     int kend = nw;
     bool moving = false;
@@ -1384,7 +1396,7 @@ __device__ __forceinline__ void aed_deflate(double *T, double *V, int ld, double
             if (tid == 0) w.mover[j] = 1;
             __syncthreads();
         }
-        const int pairs = swap_round(w, T, V, ld, nw, top, kend);
+        const int pairs = swap_round<NTH>(w, T, V, ld, nw, top, kend);
         if (pairs == 0) break;  // all movers have arrived
         if (w.rejected) {
             // the rest counts as undeflatable
@@ -1399,7 +1411,7 @@ __device__ __forceinline__ void aed_deflate(double *T, double *V, int ld, double
     for (int j = kend; j + 1 < nw;) {
         if (AT(T, ld, j + 1, j) != 0.0) {
             const double a = AT(T, ld, j, j), b = AT(T, ld, j, j + 1), c = AT(T, ld, j + 1, j), d = AT(T, ld, j + 1, j + 1);
-            if (!(a == d && b * c < 0.0)) lds_standardise(T, ld, V, ld, nw, j);
+            if (!(a == d && b * c < 0.0)) lds_standardise<NTH>(T, ld, V, ld, nw, j);
             j += 2;
         } else {
             ++j;
@@ -1442,9 +1454,9 @@ __device__ __forceinline__ void aed_deflate(double *T, double *V, int ld, double
             o.spike0 = beta;
             __syncthreads();
             if (tau != 0.0) {
-                win_refl_left(T, ld, 0, kend, 0, nw - 1, tau, x);
+                win_refl_left<NTH>(T, ld, 0, kend, 0, nw - 1, tau, x);
                 __syncthreads();
-                win_refl_right2(T, ld, kend - 1, V, nw, 0, kend, tau, x);
+                win_refl_right2<NTH>(T, ld, kend - 1, V, nw, 0, kend, tau, x);
                 __syncthreads();
             }
             // Householder Hessenberg reduction of the undeflated leading block
@@ -1455,10 +1467,10 @@ __device__ __forceinline__ void aed_deflate(double *T, double *V, int ld, double
                 win_house([&](int t) { return col[t]; }, x, len, &tau2, &beta2);
                 __syncthreads();
                 if (tau2 == 0.0) continue;
-                for (int t = tid; t < len; t += NT) col[t] = (t == 0) ? beta2 : 0.0;
-                win_refl_left(T, ld, cc + 1, len, cc + 1, nw - 1, tau2, x);
+                for (int t = tid; t < len; t += NTH) col[t] = (t == 0) ? beta2 : 0.0;
+                win_refl_left<NTH>(T, ld, cc + 1, len, cc + 1, nw - 1, tau2, x);
                 __syncthreads();
-                win_refl_right2(T, ld, kend - 1, V, nw, cc + 1, len, tau2, x);
+                win_refl_right2<NTH>(T, ld, kend - 1, V, nw, cc + 1, len, tau2, x);
                 __syncthreads();
             }
         } else {
@@ -1469,6 +1481,7 @@ __device__ __forceinline__ void aed_deflate(double *T, double *V, int ld, double
     o.cyc_hess = clock64() - c2;
 }
 
+template <int NTH = NT>
 __device__ __forceinline__ AedOut aed_core(double *T, double *V, int ld, double *x, int nw, double s, double hnorm,
                                            double smlnum, int criterion, int maxit, double *sr, double *si) {
     AedOut o;
@@ -1477,7 +1490,7 @@ __device__ __forceinline__ AedOut aed_core(double *T, double *V, int ld, double 
     o.infqr = lds_small_qr(T, ld, V, ld, nw, hnorm, smlnum, maxit, &o.iters);
     __syncthreads();
     o.cyc_qr = clock64() - c0;
-    aed_deflate(T, V, ld, x, nw, s, hnorm, smlnum, criterion, sr, si, o);
+    aed_deflate<NTH>(T, V, ld, x, nw, s, hnorm, smlnum, criterion, sr, si, o);
     return o;
 }
 
