@@ -39,11 +39,11 @@ EPS = 2.0 ** -52
 GRID = {
     "ns": [16, 32, 48, 64, 96, 128],
     "nw": [48, 64, 80, 96, 128, 192],
-    "chain": [8, 12, 16],
+    "chain": [4, 6, 8],
     "chase_w": [64, 80, 96],
     "nibble": [4, 8, 14, 25],
 }
-DEFAULT = {"ns": 32, "nw": 64, "chain": 16, "chase_w": 96, "nibble": 14}
+DEFAULT = {"ns": 32, "nw": 64, "chain": 8, "chase_w": 96, "nibble": 14}
 KEYS = tuple(DEFAULT)
 
 

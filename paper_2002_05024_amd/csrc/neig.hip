@@ -566,8 +566,8 @@ class Solver {
         const int maxit = 30 * std::max(10, nwm);
         stats_.aed_launches += 1;
         timed(kAed, [&] {
-            hipLaunchKernelGGL(k_aed, dim3(nj), dim3(NT), lds, st_, H_, ldh_, jobs, hnorm_, smlnum_, p_.deflation,
-                               maxit, nwm);
+            hipLaunchKernelGGL(k_aed, dim3(nj), dim3(AED_THREADS), lds, st_, H_, ldh_, jobs, hnorm_, smlnum_,
+                               p_.deflation, maxit, nwm);
             ck(hipGetLastError());
         });
         ck(hipMemcpyAsync(ws_.h_ist, ws_.ist, 28 * sizeof(int), hipMemcpyDeviceToHost, st_));
@@ -1282,8 +1282,8 @@ class Solver {
             ck(hipMemcpyAsync(ws_.rwin, ws_.h_rwin, (size_t)nwin * sizeof(ReorderWin), hipMemcpyHostToDevice, st_));
             const size_t lds = (size_t)(2 * W * (W + 1)) * sizeof(double);
             timed(kSmall, [&] {
-                hipLaunchKernelGGL(k_reorder_window, dim3(nwin), dim3(NT), lds, st_, H_, ldh_, ws_.rwin, ws_.vt, W,
-                                   ws_.rstat);
+                hipLaunchKernelGGL(k_reorder_window, dim3(nwin), dim3(REORDER_THREADS), lds, st_, H_, ldh_, ws_.rwin,
+                                   ws_.vt, W, ws_.rstat);
                 ck(hipGetLastError());
             });
             // left updates (rows of a window, columns right of it) touch rows the

@@ -11,13 +11,20 @@
 //    the paper cites), then a Householder Hessenberg reduction of the remaining
 //    spike and undeflated part.
 //
-// Four waves per workgroup.  In the QR iteration wave 0 works on the window alone
+// Several waves per workgroup.  In the QR iteration wave 0 works on the window alone
 // and waves 1 and 2 accumulate its reflectors into the orthogonal factor (see
-// there); other phases use all four waves with block barriers.
+// there); other phases use all waves with block barriers.
 #include "neig_dev.h"
 #include <climits>
 
 #define NT 256     // threads per workgroup; the functions below take another count as NTH
+// Waves 3 and up only help with what all waves share out: applying swaps and
+// reflectors.  Measured on MI355X with 4 / 8 / 12 waves: 64-row deflation windows,
+// spike test 755 / 672 / 629 and reduction back 284 / 238 / 263 thousand cycles, the
+// random n = 20000 reduction 825 / 796 / 798 ms; reordering n = 4000 40.1 / 36.2 /
+// 35.3 ms.  (The window QR alone, k_small_qr, has no use for them.)
+#define AED_THREADS 512
+#define REORDER_THREADS 768
 #define LANES 64   // wavefront size
 #define FB 15      // reflectors per batch handed to the accumulating waves
 
@@ -1520,7 +1527,7 @@ struct AedJobs {
 // clock cycles spent in the window QR, the spike test with its swaps, and the
 // re-Hessenberg reduction with the write-back, [10] deflations found above a
 // block that failed the test.
-extern "C" __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1)))
+extern "C" __global__ void __launch_bounds__(AED_THREADS)
 k_aed(double *H, int ldh, AedJobs jobs, double hnorm, double smlnum, int criterion, int maxit, int ldvt) {
     extern __shared__ double lds[];
     const AedJob J = jobs.j[blockIdx.x];
@@ -1534,18 +1541,18 @@ k_aed(double *H, int ldh, AedJobs jobs, double hnorm, double smlnum, int criteri
     if (!J.flip) {
         off = J.kbot - nw + 1;
         s = (off > J.ktop) ? AT(H, ldh, off, off - 1) : 0.0;
-        lds_load_block(H, ldh, off, nw, T, ld, V, ld);
+        lds_load_block<AED_THREADS>(H, ldh, off, nw, T, ld, V, ld);
     } else {
         off = J.ktop;
         s = (off + nw <= J.kbot) ? AT(H, ldh, off + nw, off + nw - 1) : 0.0;
-        for (int idx = threadIdx.x; idx < nw * nw; idx += NT) {
+        for (int idx = threadIdx.x; idx < nw * nw; idx += AED_THREADS) {
             const int i = idx % nw, j = idx / nw;
             AT(T, ld, i, j) = (i <= j + 1) ? AT(H, ldh, off + nw - 1 - j, off + nw - 1 - i) : 0.0;
             AT(V, ld, i, j) = (i == j) ? 1.0 : 0.0;
         }
         __syncthreads();
     }
-    const AedOut o = aed_core(T, V, ld, x, nw, s, hnorm, smlnum, criterion, maxit, J.sr, J.si);
+    const AedOut o = aed_core<AED_THREADS>(T, V, ld, x, nw, s, hnorm, smlnum, criterion, maxit, J.sr, J.si);
     if (threadIdx.x == 0) {
         int *status = J.status;
         status[0] = o.nd;
@@ -1562,10 +1569,10 @@ k_aed(double *H, int ldh, AedJobs jobs, double hnorm, double smlnum, int criteri
     }
     if (o.nd == 0) return;  // H untouched; only the shifts are used
     if (!J.flip) {
-        lds_store(H, ldh, off, nw, T, ld, V, ld, J.Vt, ldvt);
+        lds_store<AED_THREADS>(H, ldh, off, nw, T, ld, V, ld, J.Vt, ldvt);
         if (off > J.ktop && threadIdx.x == 0) AT(H, ldh, off, off - 1) = o.spike0;
     } else {
-        for (int idx = threadIdx.x; idx < nw * nw; idx += NT) {
+        for (int idx = threadIdx.x; idx < nw * nw; idx += AED_THREADS) {
             const int r = idx % nw, c = idx / nw;
             AT(H, ldh, off + r, off + c) = (r <= c + 1) ? AT(T, ld, nw - 1 - c, nw - 1 - r) : 0.0;
             AT(J.Vt, ldvt, r, c) = AT(V, ld, nw - 1 - c, nw - 1 - r);
@@ -1594,7 +1601,7 @@ struct ReorderWin {
 // Vt, status[0] = selected eigenvalues now at the top, status[1] = 1 if a swap
 // was rejected (the window is then partly reordered, still a valid Schur form).
 // The caller applies Vt to the rest of S and to Z.
-extern "C" __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(1, 1)))
+extern "C" __global__ void __launch_bounds__(REORDER_THREADS)
 k_reorder_window(double *S, int lds_, const ReorderWin *wins, double *Vt_all, int ldvt, int *status_all) {
     extern __shared__ double lds[];
     const ReorderWin &f = wins[blockIdx.x];
@@ -1603,13 +1610,13 @@ k_reorder_window(double *S, int lds_, const ReorderWin *wins, double *Vt_all, in
     int *status = status_all + 2 * blockIdx.x;
     const int ld = w + 1;
     double *T = lds, *V = lds + (size_t)w * ld;
-    lds_load_block(S, lds_, off, w, T, ld, V, ld);
+    lds_load_block<REORDER_THREADS>(S, lds_, off, w, T, ld, V, ld);
     // every selected block moves up past the unselected ones above it
     SwapState &sw = win_scratch().sw;
-    swap_begin(sw, T, ld, w);
-    for (int j = threadIdx.x; j < w; j += NT) sw.mover[j] = sw.head[j] && f.sel[j];
+    swap_begin<REORDER_THREADS>(sw, T, ld, w);
+    for (int j = threadIdx.x; j < w; j += REORDER_THREADS) sw.mover[j] = sw.head[j] && f.sel[j];
     __syncthreads();
-    while (swap_round(sw, T, V, ld, w, 0, w) > 0 && !sw.rejected) {
+    while (swap_round<REORDER_THREADS>(sw, T, V, ld, w, 0, w) > 0 && !sw.rejected) {
     }
     const int fail = sw.rejected;
     int placed = 0;  // selected blocks at the top
@@ -1618,13 +1625,13 @@ k_reorder_window(double *S, int lds_, const ReorderWin *wins, double *Vt_all, in
     for (int k = 0; k + 1 < w;) {
         if (AT(T, ld, k + 1, k) != 0.0) {
             const double a = AT(T, ld, k, k), b = AT(T, ld, k, k + 1), c = AT(T, ld, k + 1, k), d = AT(T, ld, k + 1, k + 1);
-            if (!(a == d && b * c < 0.0)) lds_standardise(T, ld, V, ld, w, k);
+            if (!(a == d && b * c < 0.0)) lds_standardise<REORDER_THREADS>(T, ld, V, ld, w, k);
             k += 2;
         } else {
             ++k;
         }
     }
-    lds_store(S, lds_, off, w, T, ld, V, ld, Vt, ldvt);
+    lds_store<REORDER_THREADS>(S, lds_, off, w, T, ld, V, ld, Vt, ldvt);
     if (threadIdx.x == 0) {
         status[0] = placed;
         status[1] = fail;
