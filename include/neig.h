@@ -51,7 +51,8 @@ typedef struct neig_params {
                       1: norm-stable criterion |spike| <= eps*||H||_F (Section 5)        */
     int maxit;     /* iteration limit (AED+sweep rounds); 0: 30*max(10, n)               */
     int nibble;    /* percent: an AED that deflates at least this share of its window is
-                      followed by another AED instead of a sweep                         */
+                      followed by another AED instead of a sweep; 0: by the order of the
+                      active block                                                       */
     int exc;       /* rounds without deflation before exceptional shifts                 */
     int timing;    /* 1: bracket every kernel launch with HIP events on the call's stream and
                       report per-kernel-class GPU time in neig_stats (adds host overhead) */

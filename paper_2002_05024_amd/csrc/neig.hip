@@ -277,7 +277,6 @@ class Solver {
         nbc_ = p_.chain > 0 ? p_.chain : CHASE_MAX_BULGES;
         nbc_ = std::max(1, std::min(nbc_, std::min(CHASE_MAX_BULGES, (wchase_ - 2) / 3)));
         maxit_ = p_.maxit > 0 ? p_.maxit : 30 * std::max(10, n);
-        nibble_ = p_.nibble > 0 ? p_.nibble : 14;
         exc_ = p_.exc > 0 ? p_.exc : 6;
         smlnum_ = NEIG_DBL_MIN * ((double)std::max(n, 1) / NEIG_EPS);
         stats_ = neig_stats();
@@ -949,6 +948,14 @@ class Solver {
 
     // Defaults measured on MI355X for random Hessenberg input: the AED window QR is a
     // latency-bound chain on one CU, so moderate windows deflate the most per unit time.
+    // The share of its window (percent) an AED must deflate for another AED to follow
+    // at once, for an active block of m rows.  A sweep's cost grows with m, an AED's
+    // does not, so small blocks sweep more readily.  Measured on MI355X (ms, at 14 / 20 /
+    // 33 / 45 percent): dense n = 512 65.2 / 65.3 / 52.9 / 46.0, random n = 512 21.8 /
+    // 22.6 / 21.6 / 21.8; dense n = 1500 216 / 205 / 191 / 173, random n = 1500 63.6 / 63.7
+    // / 73.9 / 77.6; random n = 5900 241 / 263 / 429 / 554.
+    int nibble_for(int m) const { return p_.nibble > 0 ? p_.nibble : (m <= 512 ? 45 : m <= 3000 ? 20 : 14); }
+
     int default_ns(int m) const {
         int ns = p_.ns > 0 ? p_.ns : (m < 300 ? 16 : 32);
         ns = std::min(ns, std::max(2, m / 3));
@@ -1157,7 +1164,7 @@ class Solver {
                     held_bins[1] = bnw;
                 }
             }
-            if (nd > 0 && 100 * nd > nibble_ * nw) continue;
+            if (nd > 0 && 100 * nd > nibble_for(m2) * nw) continue;
             int ns = default_ns(m2);
             if (ns_next > 0) {
                 ns = std::min(ns_next, std::max(2, m2 / 3));
@@ -1363,7 +1370,7 @@ class Solver {
     hipStream_t st_;
     DeviceWs &ws_;
     neig_params p_;
-    int nsmall_, nmin_, wchase_, nbc_, maxit_, nibble_, exc_;
+    int nsmall_, nmin_, wchase_, nbc_, maxit_, exc_;
     double hnorm_ = 0.0, smlnum_ = 0.0;
 };
 
@@ -1672,7 +1679,7 @@ void launch_batched_pair(int batch, const int *n, double *const *H, const int *l
         A.tune[k].ns = std::min(A.tune[k].ns, 2 * B_MAX_BULGES);
     }
     A.criterion = g_params.deflation;
-    A.nibble = g_params.nibble > 0 ? g_params.nibble : 14;
+    A.nibble = g_params.nibble;
     A.exc = g_params.exc > 0 ? g_params.exc : 6;
     A.maxit_factor = 30;
     const int grid = std::max(1, std::min(batch, cus > 0 ? cus : 256));
