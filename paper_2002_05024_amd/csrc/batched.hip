@@ -40,6 +40,16 @@ struct BTune {
     int wchase;  // chase window
 };
 
+// The method's own operation count of one problem (the same formulas as the
+// single-matrix path's neig_stats.alg_flops: 10 m^3 per window or small block solved in
+// LDS, 2 m^2 per row or column its factor is applied to, 20 n per bulge position of a
+// sweep), and what small blocks have of it.
+struct BCount {
+    double all, small;  // flops; small: the blocks' own 10 m^3
+    int solves;         // small blocks
+    int info;           // written for a problem alone
+};
+
 struct BArgs {
     const BProb *probs;
     const int *order;   // processing order (largest problems first)
@@ -48,6 +58,8 @@ struct BArgs {
                         // aligned) holds the launch's algorithmic flop count
                         // (a double), also zeroed by k_batched_pack
     int *info;          // per problem, in the caller's order
+    BProb one;          // probs null: this problem alone (tune[0]); its counts go to *count
+    struct BCount *count;
     int bucket_hi[B_NBUCKET];  // problems with n <= bucket_hi[b] use tune[b]
     BTune tune[B_NBUCKET];
     int criterion, nibble, exc, maxit_factor;
@@ -363,16 +375,14 @@ __device__ __forceinline__ int pick_shifts_dev(const double *rr, const double *r
 
 // ---------------------------------------------------------------- one problem
 
-// *flops receives the method's own operation count for this problem (the same
-// formulas as the single-matrix path's neig_stats.alg_flops: 10 m^3 per window
-// or small block solved in LDS, 2 m^2 per row or column its factor is applied
-// to, 20 n per bulge position of a sweep); every thread holds the same value.
-__device__ __forceinline__ int solve_one(const BProb &P, const BTune &tu, const BArgs &A, double *flops) {
+// *cnt receives the operation count; every thread holds the same values.
+__device__ __forceinline__ int solve_one(const BProb &P, const BTune &tu, const BArgs &A, BCount *cnt) {
     BShifts &sh = batch_shifts();
     const int tid = threadIdx.x;
     const int n = P.n;
     double *H = P.H, *Z = P.Z;
     const int ldh = P.ldh, ldz = P.ldz;
+    *cnt = {0.0, 0.0, 0, 0};
     if (n <= 0) return 0;
     double hnorm = 0.0;
     if (!wg_prep(H, ldh, n, &hnorm)) return -2;
@@ -391,6 +401,8 @@ __device__ __forceinline__ int solve_one(const BProb &P, const BTune &tu, const 
                 b_store(H, ldh, ktop, m);
                 b_update(H, ldh, Z, ldz, n, ktop, m, ktop, kbot + 1, m * (m + 1), m + 1);
                 fl += 10.0 * m * (double)m * m + 2.0 * m * (double)m * (ktop + (n - kbot - 1) + n);
+                cnt->small += 10.0 * m * (double)m * m;
+                cnt->solves++;
                 if (bad > 0) {
                     info = ktop + bad;
                     break;
@@ -540,28 +552,36 @@ __device__ __forceinline__ int solve_one(const BProb &P, const BTune &tu, const 
         }
     }
     __syncthreads();
-    *flops = fl;
+    cnt->all = fl;
     return info;
 }
 
 extern "C" __global__ void __launch_bounds__(BT) k_batched(BArgs A) {
     __shared__ int s_idx;
     for (;;) {
-        if (threadIdx.x == 0) s_idx = atomicAdd(A.next, 1);
-        __syncthreads();
-        const int k = s_idx;
-        __syncthreads();
-        if (k >= A.nprob) break;
-        const int p = A.order[k];
-        const BProb P = A.probs[p];
-        if (P.pad) continue;  // rejected by k_batched_pack (uniform across the workgroup)
-        int b = 0;
-        while (b + 1 < B_NBUCKET && P.n > A.bucket_hi[b]) ++b;
-        double fl = 0.0;
-        const int info = solve_one(P, A.tune[b], A, &fl);
+        int p = 0, b = 0;
+        BProb P = A.one;
+        if (A.probs) {
+            if (threadIdx.x == 0) s_idx = atomicAdd(A.next, 1);
+            __syncthreads();
+            const int k = s_idx;
+            __syncthreads();
+            if (k >= A.nprob) break;
+            p = A.order[k];
+            P = A.probs[p];
+            if (P.pad) continue;  // rejected by k_batched_pack (uniform across the workgroup)
+            while (b + 1 < B_NBUCKET && P.n > A.bucket_hi[b]) ++b;
+        }
+        BCount cnt;
+        const int info = solve_one(P, A.tune[b], A, &cnt);
+        if (!A.probs) {
+            cnt.info = info;
+            if (threadIdx.x == 0) *A.count = cnt;
+            break;
+        }
         if (threadIdx.x == 0) {
             A.info[p] = info;
-            atomicAdd((double *)(A.next + 2), fl);
+            atomicAdd((double *)(A.next + 2), cnt.all);
         }
         __syncthreads();
     }
