@@ -171,7 +171,7 @@ def rooflines(stats):
     """Roofline figures of the kernels from the library's per-launch HIP event
     timing: the dominant kernel (most GPU time) as ``roofline``, the others
     beside it.  Algorithmic work per launch: k_aed 10 nw^3 flops (window Schur
-    form), k_update 2 w^2 len flops per task, k_chase the bytes of its windows
+    form), k_update_p 2 w^2 len flops per task, k_chase the bytes of its windows
     (load and store of the window of H, store of U)."""
     aed_ms = sum(s["gpu_aed_ms"] for s in stats)
     # k_aed launches (one or two windows each), including those inside the

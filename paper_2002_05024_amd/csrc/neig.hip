@@ -195,8 +195,7 @@ DeviceWs &workspace() {
     w.small_max = lim.small_max;
     w.chase_max = lim.chase_max;
     for (const void *fn : {(const void *)k_small_qr, (const void *)k_aed, (const void *)k_chase,
-                           (const void *)k_update, (const void *)k_update_wide, (const void *)k_batched,
-                           (const void *)k_reorder_window})
+                           (const void *)k_update_wide, (const void *)k_batched, (const void *)k_reorder_window})
         allow_dynamic_lds(fn, w.lds_max);
     w.cus = lim.cus;
     ck(hipMalloc((void **)&w.ist, kStatusInts * sizeof(int)));
