@@ -14,7 +14,7 @@
 // A batch ends with its largest problem, so what bounds it is the time of one
 // problem on one CU.  Measured on MI355X, 512 problems of order 32 to 1024: 515 ms
 // with 4 waves (window chasing in three phases, 14200 cycles a step of 16 bulges;
-// updates through a staged tile, 1.06 million cycles a window), 234 ms now:
+// updates through a staged tile, 1.06 million cycles a window), 227 ms now:
 //  * the windows are chased by the sweep kernel's code (chase.hip: 2550 cycles a step
 //    of 8 bulges), so the workgroup has its 12 waves;
 //  * a factor is applied by each wave on its own, sixteen rows or columns at a time,
