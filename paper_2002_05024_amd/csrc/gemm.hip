@@ -289,19 +289,28 @@ __global__ void __launch_bounds__(64 * NRT) __attribute__((amdgpu_waves_per_eu(3
     UpdTask T = args.t[ti];
     double frag[NK];
     auto load_frag = [&]() {
+        // range-checked like the slices: no branch around each load
         const int rw = 16 * q + li;
+        const __amdgpu_buffer_rsrc_t rs =
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<double *>(T.Ut), (short)0, ((T.w - 1) * T.ldu + T.w) * 8,
+                                              0x00020000);
 #pragma unroll
         for (int k = 0; k < NK; ++k) {
             const int kk = 4 * k + lk;
-            frag[k] = (rw < T.w && kk < T.w) ? AT(T.Ut, T.ldu, rw, kk) : 0.0;
+            const int off = (rw < T.w && kk < T.w) ? (rw + kk * T.ldu) * 8 : UPDP_OOB;
+            frag[k] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, 0));
         }
         // complete these loads here, so that the slice loads issued later are
         // never waited for by the products that use the factor
         __builtin_amdgcn_s_waitcnt(0);
     };
-    load_frag();
+    // the first slice is requested before the factor, so that a workgroup waits for one
+    // memory latency, not two (most launches of a sweep have a slice per workgroup;
+    // with the factor's loads free of branches, n = 4000 dense form 601 -> 594 ms)
     double pre[UPDP_PER];
     updp_load<NRT>(T, s - T.tile0, pre);
+    __builtin_amdgcn_sched_barrier(0);
+    load_frag();
     for (;;) {
         __syncthreads();  // every wave is done reading the buffer
         updp_stage<NRT>(T.side, pre, lds);
