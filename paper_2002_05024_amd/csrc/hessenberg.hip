@@ -636,11 +636,13 @@ struct RkArgs {
 // C (M x N) -= L1 R1^T + L2 R2^T, in place: 64 x 64 tile per workgroup, the
 // transposed tile accumulated on the matrix cores so that each lane group
 // reads and writes 16 consecutive rows of a column; L and R staged in LDS 32
-// columns at a time.
+// columns at a time.  Bound by reading and writing C (n = 8000: 235 GB, 49 ms at the
+// rate of a large copy).  With a branch around each staged element it took 55 ms there;
+// without, and one slice ahead, the whole reduction went from 490 to 481 ms.
 extern "C" __global__ void __launch_bounds__(HRD_THREADS) k_hrd_rank(RkArgs p) {
     __shared__ double Ls[64 * HRD_PAD];
     __shared__ double Rs[64 * HRD_PAD];
-    const int t = threadIdx.x, lane = t & 63, q = t >> 6;
+    const int lane = threadIdx.x & 63, q = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int li = lane & 15, lk = lane >> 4;
     const int i0 = blockIdx.x * 64, c0 = blockIdx.y * 64;
     // lane holds D(lk + 4 rr, li) = C^T(col, row): col = c0 + 16 q + lk + 4 rr, row = i0 + 16 it + li
@@ -653,23 +655,32 @@ extern "C" __global__ void __launch_bounds__(HRD_THREADS) k_hrd_rank(RkArgs p) {
             acc[it][rr] = (row < p.M && col < p.N) ? AT(p.C, p.ldc, row, col) : 0.0;
         }
     }
+    // A slice's 16 elements per thread are loaded without branches (columns past the
+    // end count as zeros; rows past it are not stored), one slice ahead of the products.
     const int rt = p.r1 + p.r2;
+    const int lrow = min(i0 + lane, p.M - 1), rrow = min(c0 + lane, p.N - 1);
+    double lv[8], rv[8];
+    auto fetch = [&](int kc) __attribute__((always_inline)) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int k = kc + q + 4 * e, kl = min(k, rt - 1);
+            const bool second = kl >= p.r1;
+            const double *l = second ? p.L2 + (size_t)(kl - p.r1) * p.ldl2 : p.L1 + (size_t)kl * p.ldl1;
+            const double *r = second ? p.R2 + (size_t)(kl - p.r1) * p.ldr2 : p.R1 + (size_t)kl * p.ldr1;
+            lv[e] = l[lrow];
+            rv[e] = r[rrow];
+            if (k >= rt) lv[e] = rv[e] = 0.0;
+        }
+    };
+    fetch(0);
     for (int kc = 0; kc < rt; kc += 32) {
-        for (int idx = t; idx < 64 * 32; idx += HRD_THREADS) {
-            const int ii = idx & 63, kk = idx >> 6;
-            const int k = kc + kk;
-            double lv = 0.0, rv = 0.0;
-            if (k < p.r1) {
-                if (i0 + ii < p.M) lv = AT(p.L1, p.ldl1, i0 + ii, k);
-                if (c0 + ii < p.N) rv = AT(p.R1, p.ldr1, c0 + ii, k);
-            } else if (k < rt) {
-                if (i0 + ii < p.M) lv = AT(p.L2, p.ldl2, i0 + ii, k - p.r1);
-                if (c0 + ii < p.N) rv = AT(p.R2, p.ldr2, c0 + ii, k - p.r1);
-            }
-            Ls[ii * HRD_PAD + kk] = lv;
-            Rs[ii * HRD_PAD + kk] = -rv;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            Ls[lane * HRD_PAD + q + 4 * e] = lv[e];
+            Rs[lane * HRD_PAD + q + 4 * e] = -rv[e];
         }
         __syncthreads();
+        if (kc + 32 < rt) fetch(kc + 32);
 #pragma unroll
         for (int k4 = 0; k4 < 32; k4 += 4) {
             const double a = Rs[(16 * q + li) * HRD_PAD + k4 + lk];
