@@ -53,13 +53,19 @@ struct HrdArgs {
     int cw;                    // vector entries per GEMV chunk
 };
 
-// The vector that the GEMV multiplies is the column's tail times this power of
-// two, so that the products neither overflow nor underflow where A's entries do
-// not; the reflector's own scaling 1 / (alpha - beta) follows in k_hrd_a.
-__device__ __forceinline__ double hrd_scale(const HrdState *st, bool inverse) {
-    int e = (int)(st->amax >> 52) - 1023;
-    if (e == -1023 || e == 1024) e = 0;  // zero or subnormal, or not finite
-    return ldexp(1.0, inverse ? e : -e);
+// The vector that the GEMV multiplies is the column's tail times 2^-e, e this
+// exponent of max |A|, so that the products neither overflow nor underflow where A's
+// entries do not; the reflector's own scaling 1 / (alpha - beta) follows in k_hrd_a.
+__device__ __forceinline__ int hrd_exponent(const HrdState *st) {
+    const int e = (int)(st->amax >> 52) - 1023;
+    return e == -1023 || e == 1024 ? 0 : e;  // zero or subnormal, or not finite
+}
+
+// The tails are multiplied by 2^this before k_hrd_b's sums V^T (tail): as far up as
+// the sums allow (a tail's norm is at most max |A| n < 2^17 max |A|), so that a
+// subnormal tail's products with V keep their bits, on which V's orthogonality rests.
+__device__ __forceinline__ int hrd_lift(const HrdState *st) {
+    return max(0, 980 - ((int)(st->amax >> 52) - 1023));
 }
 
 extern "C" __global__ void k_hrd_begin(HrdState *st) {
@@ -157,6 +163,7 @@ __global__ void __launch_bounds__(HRD_THREADS * RG) k_hrd_a(HrdArgs p) {
     __shared__ double red[NW][HRD_NB];
     __shared__ double comb[3][4][64 * RG];
     __shared__ double us[HRD_NB], vs[HRD_NB], coef[3];
+    __shared__ int cexp;
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6), q = wave & 3, g = wave >> 2;
     const int i = p.i, ip = i - 1, j = p.k0 + i;
@@ -219,34 +226,42 @@ __global__ void __launch_bounds__(HRD_THREADS * RG) k_hrd_a(HrdArgs p) {
         for (int b = lane + 128; b < nblk * RG; b += 64) mx = fmax(mx, p.spart[2 * b]);
         mx = wave_max(mx);
         double beta = alpha, tau = 0.0, scal = 0.0;
+        int ex = 0;
         if (mx > 0.0) {
             const int em = ilogb(mx);
-            const double inv = ldexp(1.0, -em);
-            double sq = nsq[0] * (nsc[0] * inv) * (nsc[0] * inv) + nsq[1] * (nsc[1] * inv) * (nsc[1] * inv);
+            // by exponents, not by a reciprocal: 2^-em overflows for a subnormal tail
+            const double f0 = ldexp(nsc[0], -em), f1 = ldexp(nsc[1], -em);
+            double sq = nsq[0] * f0 * f0 + nsq[1] * f1 * f1;
             for (int b = lane + 128; b < nblk * RG; b += 64) {
-                const double f = p.spart[2 * b] * inv;
+                const double f = ldexp(p.spart[2 * b], -em);
                 sq += p.spart[2 * b + 1] * f * f;
             }
             sq = wave_sum(sq);
-            // the norm with alpha, both scaled to the larger exponent
+            // the norm with alpha, and the reflector, both scaled by 2^-ex, the
+            // larger exponent (1 / (alpha - beta) itself may overflow)
             const int ea = alpha != 0.0 && isfinite(alpha) ? ilogb(alpha) : em;
-            const int e = max(ea, em);
-            const double as = ldexp(alpha, -e);
-            const double nrm = ldexp(sqrt(as * as + ldexp(sq, 2 * max(em - e, -600))), e);
-            beta = alpha >= 0.0 ? -nrm : nrm;
-            tau = (beta - alpha) / beta;
-            scal = 1.0 / (alpha - beta);
+            ex = max(ea, em);
+            const double as = ldexp(alpha, -ex);
+            const double nrm = sqrt(as * as + ldexp(sq, 2 * max(em - ex, -600)));
+            const double bs = alpha >= 0.0 ? -nrm : nrm;
+            beta = ldexp(bs, ex);
+            tau = (bs - as) / bs;
+            scal = 1.0 / (as - bs);
         }
         vs[lane] = lane < ip ? vr : 0.0;
         if (lane == 0) {
             coef[0] = beta;
             coef[1] = tau;
             coef[2] = scal;
+            cexp = ex;
         }
     }
     __syncthreads();
+    // v = 2^-ex (tail) scal
     const double beta = coef[0], tau = coef[1], scal = coef[2];
-    if (t < HRD_NB) us[t] = t < ip ? vs[t] + scal * hrd_add_waves<NW>(red, t) : 0.0;
+    const int ex = cexp;
+    if (t < HRD_NB)
+        us[t] = t < ip ? vs[t] + ldexp(scal * hrd_add_waves<NW>(red, t), -ex - hrd_lift(p.st)) : 0.0;
     __syncthreads();
     double yu = 0.0, yw = 0.0;
 #pragma unroll
@@ -276,8 +291,8 @@ __global__ void __launch_bounds__(HRD_THREADS * RG) k_hrd_a(HrdArgs p) {
     z = (comb[0][0][lr] + comb[0][1][lr]) + (comb[0][2][lr] + comb[0][3][lr]);
     yu = (comb[1][0][lr] + comb[1][1][lr]) + (comb[1][2][lr] + comb[1][3][lr]);
     yw = (comb[2][0][lr] + comb[2][1][lr]) + (comb[2][2][lr] + comb[2][3][lr]);
-    const double vnew = r < ip ? 0.0 : (r == ip ? 1.0 : old * scal);
-    const double ycol = tau * ((aj + (z * scal) * hrd_scale(p.st, true)) - yu);
+    const double vnew = r < ip ? 0.0 : (r == ip ? 1.0 : ldexp(old, -ex) * scal);
+    const double ycol = tau * ((aj + ldexp(z * scal, hrd_exponent(p.st) - ex)) - yu);
     const double a = aj - (yw + ycol);  // V(i-1, i-1) = 1
     if (q == 0 && in) {
         AT(p.V, p.ldw, r, ip) = vnew;
@@ -360,8 +375,9 @@ __global__ void __launch_bounds__(HRD_THREADS * RG) k_hrd_b(HrdArgs p) {
         }
     }
     double x[16];
+    const double lifted = ldexp(tail, hrd_lift(p.st));
 #pragma unroll
-    for (int e = 0; e < 16; ++e) x[e] = vv[e] * tail;
+    for (int e = 0; e < 16; ++e) x[e] = vv[e] * lifted;
     __syncthreads();  // red is free
     hrd_store_part<RG>(hrd_sum16(x, lane), p.upart, red, lane, q, g);
 }
@@ -388,8 +404,8 @@ extern "C" __global__ void __launch_bounds__(HRD_THREADS) k_hrd_gemv_small(HrdAr
     // the first sixteen columns are on their way while the vector is staged
 #pragma unroll
     for (int u = 0; u < 16; ++u) x[u] = col[(size_t)min(f + u, cn - 1) * ld];
-    const double scale = hrd_scale(p.st, false);
-    if (t < p.cw) v[t] = t < cn ? AT(p.A, p.lda, base + c0 + t, p.k0 + p.i) * scale : 0.0;
+    const int e = hrd_exponent(p.st);
+    if (t < p.cw) v[t] = t < cn ? ldexp(AT(p.A, p.lda, base + c0 + t, p.k0 + p.i), -e) : 0.0;
     __syncthreads();
     double a0 = 0.0, a1 = 0.0;
     for (int c = f; c < l; c += 16) {
@@ -416,8 +432,8 @@ extern "C" __global__ void __launch_bounds__(HRD_THREADS) k_hrd_gemv(HrdArgs p) 
     const int cn = min(p.cw, p.m - c0);
     const int j = p.k0 + p.i;
     const size_t base = (size_t)p.k0 + 1;
-    const double scal = hrd_scale(p.st, false);
-    for (int u = t; u < cn; u += HRD_THREADS) v[u] = AT(p.A, p.lda, base + c0 + u, j) * scal;
+    const int e = hrd_exponent(p.st);
+    for (int u = t; u < cn; u += HRD_THREADS) v[u] = ldexp(AT(p.A, p.lda, base + c0 + u, j), -e);
     __syncthreads();
     const int r0 = blockIdx.x * HRD_GR + t, r1 = r0 + HRD_THREADS;
     const bool in0 = r0 < p.m, in1 = r1 < p.m;
