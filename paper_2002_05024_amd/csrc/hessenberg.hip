@@ -53,12 +53,14 @@ struct HrdArgs {
     int cw;                    // vector entries per GEMV chunk
 };
 
-// The vector that the GEMV multiplies is the column's tail times 2^-e, e this
-// exponent of max |A|, so that the products neither overflow nor underflow where A's
-// entries do not; the reflector's own scaling 1 / (alpha - beta) follows in k_hrd_a.
-__device__ __forceinline__ int hrd_exponent(const HrdState *st) {
-    const int e = (int)(st->amax >> 52) - 1023;
-    return e == -1023 || e == 1024 ? 0 : e;  // zero or subnormal, or not finite
+// The vector that the product multiplies is the column's tail times 2^-e, e from the
+// tail's own largest exponent and its length, so that its norm is at most 1 and its
+// largest entry at least 1 / (4 sqrt m): as safe from overflow and underflow as v
+// itself, whatever the column's size beside A's.  The reflector's scaling, which is not
+// known yet, follows in k_hrd_a.
+// mx: the largest of the scales that k_hrd_b left, 2^em (or 0: no tail).
+__device__ __forceinline__ int hrd_exponent(double mx, int m) {
+    return __builtin_amdgcn_frexp_exp(mx) + (33 - __clz(m)) / 2;
 }
 
 // The tails are multiplied by 2^this before k_hrd_b's sums V^T (tail): as far up as
@@ -163,7 +165,7 @@ __global__ void __launch_bounds__(HRD_THREADS * RG) k_hrd_a(HrdArgs p) {
     __shared__ double red[NW][HRD_NB];
     __shared__ double comb[3][4][64 * RG];
     __shared__ double us[HRD_NB], vs[HRD_NB], coef[3];
-    __shared__ int cexp;
+    __shared__ int cexp[2];
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6), q = wave & 3, g = wave >> 2;
     const int i = p.i, ip = i - 1, j = p.k0 + i;
@@ -174,6 +176,7 @@ __global__ void __launch_bounds__(HRD_THREADS * RG) k_hrd_a(HrdArgs p) {
     const size_t gr = (size_t)p.k0 + 1 + rr;
     const bool last = i == p.jb;  // the panel's last launch only finishes reflector i-1
     const int nblk = gridDim.x;
+    const int lift = hrd_lift(p.st);
     // the first wave's part of the reflector: its loads go out before all others
     double nsc[2], nsq[2], alpha = 0.0, vr = 0.0;
 #pragma unroll
@@ -253,15 +256,16 @@ __global__ void __launch_bounds__(HRD_THREADS * RG) k_hrd_a(HrdArgs p) {
             coef[0] = beta;
             coef[1] = tau;
             coef[2] = scal;
-            cexp = ex;
+            cexp[0] = ex;
+            cexp[1] = hrd_exponent(mx, p.m) - ex;
         }
     }
     __syncthreads();
     // v = 2^-ex (tail) scal
     const double beta = coef[0], tau = coef[1], scal = coef[2];
-    const int ex = cexp;
+    const int ex = cexp[0], ez = cexp[1];
     if (t < HRD_NB)
-        us[t] = t < ip ? vs[t] + ldexp(scal * hrd_add_waves<NW>(red, t), -ex - hrd_lift(p.st)) : 0.0;
+        us[t] = t < ip ? vs[t] + ldexp(scal * hrd_add_waves<NW>(red, t), -ex - lift) : 0.0;
     __syncthreads();
     double yu = 0.0, yw = 0.0;
 #pragma unroll
@@ -292,7 +296,7 @@ __global__ void __launch_bounds__(HRD_THREADS * RG) k_hrd_a(HrdArgs p) {
     yu = (comb[1][0][lr] + comb[1][1][lr]) + (comb[1][2][lr] + comb[1][3][lr]);
     yw = (comb[2][0][lr] + comb[2][1][lr]) + (comb[2][2][lr] + comb[2][3][lr]);
     const double vnew = r < ip ? 0.0 : (r == ip ? 1.0 : ldexp(old, -ex) * scal);
-    const double ycol = tau * ((aj + ldexp(z * scal, hrd_exponent(p.st) - ex)) - yu);
+    const double ycol = tau * ((aj + ldexp(z * scal, ez)) - yu);
     const double a = aj - (yw + ycol);  // V(i-1, i-1) = 1
     if (q == 0 && in) {
         AT(p.V, p.ldw, r, ip) = vnew;
@@ -324,6 +328,7 @@ __global__ void __launch_bounds__(HRD_THREADS * RG) k_hrd_b(HrdArgs p) {
     const bool in = r < p.m;
     const int rr = in ? r : p.m - 1;
     const size_t gr = (size_t)p.k0 + 1 + rr;
+    const int lift = hrd_lift(p.st);
     double vv[16];
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
@@ -375,14 +380,14 @@ __global__ void __launch_bounds__(HRD_THREADS * RG) k_hrd_b(HrdArgs p) {
         }
     }
     double x[16];
-    const double lifted = ldexp(tail, hrd_lift(p.st));
+    const double lifted = ldexp(tail, lift);
 #pragma unroll
     for (int e = 0; e < 16; ++e) x[e] = vv[e] * lifted;
     __syncthreads();  // red is free
     hrd_store_part<RG>(hrd_sum16(x, lane), p.upart, red, lane, q, g);
 }
 
-// z(r) = sum over the chunk's entries c of A(k0+1+r, k0+1+c) * scale * a(c),
+// z(r) = sum over the chunk's entries c of A(k0+1+r, k0+1+c) * 2^-e a(c),
 // a = column j's tail (local entries i+1..m-1).  Grid: row blocks x chunks.
 // k_hrd_gemv_small, for trailing blocks whose large tiles would leave compute units
 // idle: 64 rows per workgroup, the chunk's columns split over its four waves.
@@ -401,11 +406,14 @@ extern "C" __global__ void __launch_bounds__(HRD_THREADS) k_hrd_gemv_small(HrdAr
     const double *col = p.A + (base + c0) * (size_t)p.lda + base + rr;
     double x[16];
     const size_t ld = (size_t)p.lda;
-    // the first sixteen columns are on their way while the vector is staged
+    // the scales (one per lane: at most 64 groups of rows here), the vector, and the
+    // first sixteen columns are on their way together
+    const double sc = p.spart[2 * min(lane, (p.m + 63) / 64 - 1)];
+    const double a = AT(p.A, p.lda, base + c0 + min(t, cn - 1), p.k0 + p.i);
 #pragma unroll
     for (int u = 0; u < 16; ++u) x[u] = col[(size_t)min(f + u, cn - 1) * ld];
-    const int e = hrd_exponent(p.st);
-    if (t < p.cw) v[t] = t < cn ? ldexp(AT(p.A, p.lda, base + c0 + t, p.k0 + p.i), -e) : 0.0;
+    const int e = hrd_exponent(wave_max(sc), p.m);
+    if (t < p.cw) v[t] = t < cn ? ldexp(a, -e) : 0.0;
     __syncthreads();
     double a0 = 0.0, a1 = 0.0;
     for (int c = f; c < l; c += 16) {
@@ -432,7 +440,9 @@ extern "C" __global__ void __launch_bounds__(HRD_THREADS) k_hrd_gemv(HrdArgs p) 
     const int cn = min(p.cw, p.m - c0);
     const int j = p.k0 + p.i;
     const size_t base = (size_t)p.k0 + 1;
-    const int e = hrd_exponent(p.st);
+    double mx = 0.0;
+    for (int b = t & 63; b < (p.m + 63) / 64; b += 64) mx = fmax(mx, p.spart[2 * b]);
+    const int e = hrd_exponent(wave_max(mx), p.m);
     for (int u = t; u < cn; u += HRD_THREADS) v[u] = ldexp(AT(p.A, p.lda, base + c0 + u, j), -e);
     __syncthreads();
     const int r0 = blockIdx.x * HRD_GR + t, r1 = r0 + HRD_THREADS;

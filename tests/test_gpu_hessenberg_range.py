@@ -1,6 +1,7 @@
 """Hessenberg reduction of finite inputs whose columns lie far from the rest of the
-matrix: first columns whose tail is subnormal, beside an ordinary subdiagonal entry,
-a zero one and a subnormal one.  Orders on both sides of 4096, where the column kernels
+matrix: a first column far below max |A| (its reflector has entries of ordinary size
+all the same), and first columns whose tail is subnormal, beside an ordinary subdiagonal
+entry and beside a zero one.  Orders on both sides of 4096, where the column kernels
 and the matrix-vector product change their tiles.  A Householder reduction is backward
 stable column by column whatever the columns' sizes, so the bounds are the ones of the
 other Hessenberg tests: backward error and orthogonality within 50 n eps.  (Entries at
@@ -27,6 +28,19 @@ def reduce(A):
     Ad = neig.colmajor(A, "cuda:0")
     Q = neig.hessenberg(Ad)
     return Ad, Q, bool(torch.isfinite(Ad).all()) and bool(torch.isfinite(Q).all())
+
+
+@pytest.mark.parametrize("n", ORDERS)
+@pytest.mark.parametrize("big,small", [(66, -997), (664, -392), (664, -498), (900, -300), (0, -1010)])
+def test_column_far_below_the_matrix(n, big, small):
+    """max |A| about 2^big, the first column about 2^small."""
+    A = np.ldexp(normal(n, n), big)
+    A[:, 0] = np.ldexp(normal(n, n)[:, 0], small)
+    H, Q, finite = reduce(A)
+    assert finite
+    down = [neig.colmajor(np.ldexp(M, -big), "cuda:0") for M in (A, H.cpu().numpy())]
+    assert gpu_backward_error(*down, Q) <= 50 * n * EPS
+    assert gpu_orthogonality(Q) <= 50 * n * EPS
 
 
 @pytest.mark.parametrize("n", ORDERS)
