@@ -306,14 +306,15 @@ __device__ __attribute__((noinline)) int b_deflate(double *H, int ldh, int ktop,
 
 // One window of a sweep; its factor stays in LDS behind the window.
 __device__ __attribute__((noinline)) void b_chase(double *H, int ldh, int ktop, int kbot, int r0, int r1, int t0, int t1,
-                                                  int nb, int bulge0) {
+                                                  int nb, int bulge0, unsigned span) {
     extern __shared__ double lds[];
     H = uni(H); ldh = uni(ldh); ktop = uni(ktop); kbot = uni(kbot);
     ChaseWin W;
     W.r0 = uni(r0); W.r1 = uni(r1); W.t0 = uni(t0); W.t1 = uni(t1); W.nb = uni(nb);
     W.chain = 0;
     const int mb = W.r1 - ((W.r0 > 0) ? W.r0 - 1 : 0) + 1;
-    chase_window(H, ldh, W, ktop, kbot, batch_shifts().poly + 2 * uni(bulge0), lds, lds + (size_t)mb * (mb | 1));
+    chase_window(H, ldh, W, ktop, kbot, batch_shifts().poly + 2 * uni(bulge0), (unsigned)uni((int)span), lds,
+                 lds + (size_t)mb * (mb | 1));
 }
 
 // ---------------------------------------------------------------- shifts (thread 0)
@@ -490,7 +491,7 @@ __device__ __forceinline__ int solve_one(const BProb &P, const BTune &tu, const 
                 const int t1 = (r1 < kbot) ? r1 - 3 - ktop + 1 : tend + 1;
                 const int b0 = (r0 > 0) ? r0 - 1 : 0;
                 const int mb = r1 - b0 + 1, w = r1 - r0 + 1;
-                b_chase(H, ldh, ktop, kbot, r0, r1, t, t1, nb, c0);
+                b_chase(H, ldh, ktop, kbot, r0, r1, t, t1, nb, c0, refl_span(hnorm));
                 b_update(H, ldh, Z, ldz, n, r0, w, b0, r1 + 1, mb * (mb | 1), w | 1);
                 t = t1;
             }

@@ -55,12 +55,14 @@ struct ChaseArgs {
     int ktop, kbot;
     int nbc;   // bulges per full chain
     int ldut;  // leading dimension (and slot stride ldut*ldut) of the U^T outputs
+    unsigned span;  // refl_span of ||H||_F, or REFL_LOCAL: of each window by itself
 };
 
 // Reflector of the bulge introduced at ktop (shifts of its polynomial
 // z^2 - tr z + det, scaled), from the leading 3 x 2 corner of the active block
 // (local index p of row ktop).
-__device__ __forceinline__ ReflU chase_intro(const double *Hs, int ldhs, int p, int m3, double tr, double det) {
+__device__ __forceinline__ ReflU chase_intro(const double *Hs, int ldhs, int p, int m3, double tr, double det,
+                                             unsigned span) {
     const double h00 = AT(Hs, ldhs, p, p), h01 = AT(Hs, ldhs, p, p + 1);
     const double h10 = AT(Hs, ldhs, p + 1, p), h11 = AT(Hs, ldhs, p + 1, p + 1);
     const double h21 = (m3 == 3) ? AT(Hs, ldhs, p + 2, p + 1) : 0.0;
@@ -70,7 +72,7 @@ __device__ __forceinline__ ReflU chase_intro(const double *Hs, int ldhs, int p, 
     const double rs = 1.0 / sc;
     const double aa = h00 * rs, bb = h01 * rs, cc = h10 * rs, dd = h11 * rs, ee = h21 * rs;
     const double tt = tr * rs, dt = det * rs * rs;
-    return refl_u(gen_vec(aa * aa + bb * cc - tt * aa + dt, cc * (aa + dd - tt), cc * ee));
+    return refl_u(gen_vec(aa * aa + bb * cc - tt * aa + dt, cc * (aa + dd - tt), cc * ee, span));
 }
 
 // One batch of reflectors c[step][bulge] on one far row (on: this lane has one) of M
@@ -158,7 +160,7 @@ __device__ __forceinline__ void chase_left3(double *e, bool on, const ReflU &r) 
 // A three-row reflector from the right on the zone's rows up to pos+3 (lane lx holds
 // row pos+1, e its entry in column pos), and the bulge's next reflector from what
 // column pos then holds in rows pos+1..pos+3.
-__device__ __forceinline__ void chase_right3(double *e, int ld, int lane, int lx, ReflU &r) {
+__device__ __forceinline__ void chase_right3(double *e, int ld, int lane, int lx, unsigned span, ReflU &r) {
     const bool on = lane <= lx + 2;
     double x0 = 0.0, x1 = 0.0, x2 = 0.0;
     if (on) {
@@ -170,7 +172,7 @@ __device__ __forceinline__ void chase_right3(double *e, int ld, int lane, int lx
     x0 = fma(s, r.u0, x0);
     x1 = fma(s, r.u1, x1);
     x2 = fma(s, r.u2, x2);
-    const GenVec g = gen_vec(lane_value(x0, lx), lane_value(x0, lx + 1), lane_value(x0, lx + 2));
+    const GenVec g = gen_vec(lane_value(x0, lx), lane_value(x0, lx + 1), lane_value(x0, lx + 2), span);
     if (on) {
         e[ld] = x1;
         e[2 * ld] = x2;
@@ -182,7 +184,8 @@ __device__ __forceinline__ void chase_right3(double *e, int ld, int lane, int lx
 
 // The near waves' part of one window: wave b chases bulge b.
 __device__ __forceinline__ void chase_near(double *Hs, int ldhs, int mb, int b0, const ChaseWin &W, int ktop, int kbot,
-                                           const double *poly, double (*cq)[CHASE_BATCH][CHASE_MAX_BULGES][4], int b) {
+                                           const double *poly, unsigned span,
+                                           double (*cq)[CHASE_BATCH][CHASE_MAX_BULGES][4], int b) {
     const int lane = threadIdx.x & 63;
     const bool wide = W.r1 - W.r0 >= 64;
     int pos = ktop + W.t0 - 3 * b;
@@ -191,10 +194,10 @@ __device__ __forceinline__ void chase_near(double *Hs, int ldhs, int mb, int b0,
     if (act) {  // the reflector of the window's first step
         const int p = pos - b0, m3 = (pos <= kbot - 2) ? 3 : 2;
         if (pos == ktop) {
-            r = chase_intro(Hs, ldhs, p, m3, poly[2 * b], poly[2 * b + 1]);
+            r = chase_intro(Hs, ldhs, p, m3, poly[2 * b], poly[2 * b + 1], span);
         } else {
             double *c = &AT(Hs, ldhs, p, p - 1);
-            r = refl_u(gen_vec(c[0], c[1], m3 == 3 ? c[2] : 0.0));
+            r = refl_u(gen_vec(c[0], c[1], m3 == 3 ? c[2] : 0.0, span));
             if (lane < m3) c[lane] = lane == 0 ? r.beta : 0.0;
         }
     }
@@ -209,6 +212,9 @@ __device__ __forceinline__ void chase_near(double *Hs, int ldhs, int mb, int b0,
             // active block: no case distinctions in the steps
             int p = pos - b0;
             double *el = Hs + p + c0 * ldhs, *er = Hs + z0 + lane + p * ldhs, *c = cq[buf][0][b];
+            // the loop starts 16 bytes into a unit of 32 (n = 4000 dense form: the chase
+            // launches take 220.4 ms, 224.3 to 224.8 from its beginning or off by 4)
+            asm volatile(".p2align 5\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0");
 #pragma unroll 1
             for (int s = 0; s < CHASE_BATCH; ++s) {
                 chase_left3(el, c0 >= p && c0 < mb, r);
@@ -217,7 +223,7 @@ __device__ __forceinline__ void chase_near(double *Hs, int ldhs, int mb, int b0,
                     c[0] = r.q; c[1] = r.u0; c[2] = r.u1; c[3] = r.u2;
                 }
                 __syncthreads();
-                chase_right3(er, ldhs, lane, p + 1 - z0, r);
+                chase_right3(er, ldhs, lane, p + 1 - z0, span, r);
                 __syncthreads();
                 ++p;
                 ++el;
@@ -254,7 +260,7 @@ __device__ __forceinline__ void chase_near(double *Hs, int ldhs, int mb, int b0,
             // right: the zone's rows up to pos+3 of columns pos..pos+2; the next reflector
             double *e = Hs + z0 + lane + p * ldhs;
             if (act && more && pos + 3 <= kbot) {
-                chase_right3(e, ldhs, lane, lx, r);
+                chase_right3(e, ldhs, lane, lx, span, r);
             } else if (act) {
                 const bool on = z0 + lane <= min(pos + 3, kbot) - b0;
                 const bool build = more && pos + 1 <= kbot - 1;
@@ -274,7 +280,7 @@ __device__ __forceinline__ void chase_near(double *Hs, int ldhs, int mb, int b0,
                     if (three) e[2 * ldhs] = x2;
                 }
                 if (build) {  // pos + 3 > kbot: rows pos+1, pos+2 of column pos
-                    r = refl_u(gen_vec(lane_value(x0, lx), lane_value(x0, lx + 1), 0.0));
+                    r = refl_u(gen_vec(lane_value(x0, lx), lane_value(x0, lx + 1), 0.0, span));
                     if (on && lane >= lx) e[0] = lane == lx ? r.beta : 0.0;
                 }
             }
@@ -283,7 +289,7 @@ __device__ __forceinline__ void chase_near(double *Hs, int ldhs, int mb, int b0,
             if (!act) r.q = r.u0 = r.u1 = r.u2 = 0.0;
             __syncthreads();
             if (act && pos == ktop)  // enters with the next step
-                r = chase_intro(Hs, ldhs, ktop - b0, (ktop <= kbot - 2) ? 3 : 2, poly[2 * b], poly[2 * b + 1]);
+                r = chase_intro(Hs, ldhs, ktop - b0, (ktop <= kbot - 2) ? 3 : 2, poly[2 * b], poly[2 * b + 1], span);
         }
         if (tb + CHASE_BATCH >= W.t1) break;
     }
@@ -326,7 +332,7 @@ __device__ __forceinline__ void chase_far_rows(double *Hs, int ldhs, int mb, dou
 // Hs and Us take mb and w columns of odd length; U stays in Us (leading dimension
 // w | 1); ends with a barrier.
 __device__ __forceinline__ void chase_window(double *H, int ldh, const ChaseWin &W, int ktop, int kbot,
-                                             const double *poly, double *Hs, double *Us) {
+                                             const double *poly, unsigned span, double *Hs, double *Us) {
     __shared__ double cq[2][CHASE_BATCH][CHASE_MAX_BULGES][4];  // two batches' reflectors (q, u0, u1, u2)
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -361,12 +367,18 @@ __device__ __forceinline__ void chase_window(double *H, int ldh, const ChaseWin 
             if (j < mb && lane < mb) AT(Hs, ldhs, lane, j) = x[c][0];
             if (j < mb && lane + 64 < mb) AT(Hs, ldhs, lane + 64, j) = x[c][1];
         }
+        if (span == REFL_LOCAL) {
+            double mx = 0.0;
+#pragma unroll
+            for (int c = 0; c < PER; ++c) mx = fmax(mx, fmax(fabs(x[c][0]), tall ? fabs(x[c][1]) : 0.0));
+            span = refl_span((NEIG_CHASE_MAX + 1) * block_reduce<CHASE_THREADS>(mx, true));
+        }
     }
     __syncthreads();
     // both kinds of waves meet the same barriers: one before the first step, two
     // per step, one after the last
     if (wave < CHASE_NEAR) {
-        chase_near(Hs, ldhs, mb, b0, W, ktop, kbot, poly, cq, wave);
+        chase_near(Hs, ldhs, mb, b0, W, ktop, kbot, poly, span, cq, wave);
         __syncthreads();
     } else {
         chase_far_rows(Hs, ldhs, mb, Us, ldus, b0, W, ktop, cq, wave - CHASE_NEAR);
@@ -390,7 +402,7 @@ k_chase(double *H, int ldh, const double *poly, double *Ut, ChaseArgs a) {
     const ChaseWin W = a.win[blockIdx.x];
     const int mb = W.r1 - ((W.r0 > 0) ? W.r0 - 1 : 0) + 1, w = W.r1 - W.r0 + 1;
     double *Us = lds + (size_t)mb * (mb | 1);
-    chase_window(H, ldh, W, a.ktop, a.kbot, poly + 2 * (size_t)W.chain * a.nbc, lds, Us);
+    chase_window(H, ldh, W, a.ktop, a.kbot, poly + 2 * (size_t)W.chain * a.nbc, a.span, lds, Us);
     double *Uo = Ut + (size_t)blockIdx.x * a.ldut * a.ldut;
     const int lane = threadIdx.x & 63;
     for (int c = threadIdx.x >> 6; c < w; c += CHASE_THREADS / 64) {

@@ -809,6 +809,7 @@ class Solver {
             ChaseArgs ca;
             std::memset(&ca, 0, sizeof(ca));
             ca.ktop = ktop; ca.kbot = kbot; ca.nbc = nbc; ca.ldut = ldut;
+            ca.span = hnorm_ >= 0.0 ? refl_span(hnorm_) : REFL_LOCAL;
             int prev_r0 = 0;
             bool prev_done = true, prev_ran = false;
             int nact = 0;
@@ -1402,7 +1403,8 @@ class Solver {
     DeviceWs &ws_;
     neig_params p_;
     int nsmall_, nmin_, wchase_, nbc_, maxit_, exc_;
-    double hnorm_ = 0.0, smlnum_ = 0.0;
+    double hnorm_ = -1.0;  // ||H||_F once prep() ran (a sweep by itself does without)
+    double smlnum_ = 0.0;
 };
 
 // ---------------------------------------------------------------- Hessenberg reduction

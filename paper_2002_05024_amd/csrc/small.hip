@@ -157,10 +157,18 @@ struct GenVec {
     double x0, x1, x2, a, sc;
 };
 
-__device__ __forceinline__ GenVec gen_vec(double x0, double x1, double x2) {
+// The range of a in which u stays as it is: (2^-664, 2^664), |u| in (2^-332, 2^333).
+// The products with the matrix's entries x are then at most |u| |x| and |x| / |u|, so
+// they stay finite while ||H||_F < 2^600 (similarity transforms keep the norm); above,
+// every vector is scaled, and u is of order 1 as v of I - tau v v^T is.
+#define REFL_SPAN 0x53000000u
+#define REFL_LOCAL 1u  // stands for the span of a window whose norm the host does not know
+__host__ __device__ inline unsigned refl_span(double hnorm) { return hnorm < 0x1p600 ? REFL_SPAN : 0u; }
+
+__device__ __forceinline__ GenVec gen_vec(double x0, double x1, double x2, unsigned span) {
     GenVec g{x0, x1, x2, fma(x0, x0, fma(x1, x1, x2 * x2)), 1.0};
-    // a in about (1e-200, 1e200), by its exponent; the same in every lane
-    if (__builtin_expect(__ballot((unsigned)__double2hiint(g.a) - 0x16700000u < 0x53000000u) == 0ull, 0)) {
+    // by the exponent of a; the same in every lane
+    if (__builtin_expect(__ballot((unsigned)__double2hiint(g.a) - 0x16700000u < span) == 0ull, 0)) {
         const double mx = fmax(fabs(x0), fmax(fabs(x1), fabs(x2)));
         if (mx > 0.0 && mx < INFINITY) {
             const int e = ilogb(mx);
@@ -273,8 +281,8 @@ __device__ __forceinline__ void qr_accumulate(QrQueue &q, int who, double *Q, in
 // queue's entries.  ldt > m: row m of T is never read as data, and takes the
 // stores of lanes that hold nothing.
 template <int SETS>
-__device__ __forceinline__ void qr_sweep(double *T, int ldt, int m, int l, int i, double tr, double det, QrQueue &q,
-                                         int nacc, int &entry) {
+__device__ __forceinline__ void qr_sweep(double *T, int ldt, int m, int l, int i, double tr, double det, unsigned span,
+                                         QrQueue &q, int nacc, int &entry) {
     const int lane = threadIdx.x & (LANES - 1);
     double C[3][3], x0, x1, x2;
 #pragma unroll
@@ -401,14 +409,14 @@ __device__ __forceinline__ void qr_sweep(double *T, int ldt, int m, int l, int i
         record(r, first);
     };
     int k = l;
-    core_step(gen_vec(x0, x1, x2), k, true, k < i - 2);
+    core_step(gen_vec(x0, x1, x2, span), k, true, k < i - 2);
     ++k;
     // One step: the range check of its reflector, then the lanes' part of the step
     // before it between the dependent operations of this one's reflector.  The
     // scheduling barriers keep that order (left alone, the compiler issues the
     // reflector's chain in one piece, with a wait at every operation).
     auto step = [&](bool more) __attribute__((always_inline)) {
-        const GenVec x = gen_vec(x0, x1, x2);
+        const GenVec x = gen_vec(x0, x1, x2, span);
         const double q = r.q, u0 = r.u0, u1 = r.u1, u2 = r.u2;  // step k - 1
         double vv[SETS][3], t[SETS];
         const double y = __builtin_amdgcn_rsq(x.a);
@@ -528,7 +536,11 @@ __device__ __forceinline__ void qr_sweep(double *T, int ldt, int m, int l, int i
     };
     while (k < i - 2) {
         const int ke = min(i - 2, k0 + FB);
-        while (k + 3 <= ke) {  // by three, so that the shifts cost no moves
+        // by three, so that the shifts cost no moves; the loop starts on a multiple of 8
+        // bytes (64-row windows: 23 430 cycles a sweep, 23 910 where the code before it
+        // ended half way, as most of its instructions then straddle two such units)
+        asm volatile(".p2align 6");
+        while (k + 3 <= ke) {
             step(true);
             step(true);
             step(true);
@@ -541,7 +553,7 @@ __device__ __forceinline__ void qr_sweep(double *T, int ldt, int m, int l, int i
     lanes_step(r, J, k - 1, false);
     // the last, two-row reflector at k = i - 1, on core rows 0, 1 and columns 0, 1
     {
-        const ReflU e = refl_u(gen_vec(x0, x1, 0.0));
+        const ReflU e = refl_u(gen_vec(x0, x1, 0.0, span));
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
             const double t = e.q * fma(e.u0, C[0][b], e.u1 * C[1][b]);
@@ -607,6 +619,7 @@ template <int SETS>
 __device__ __forceinline__ int qr_iterate(double *T, int ldt, int m, double hnorm, double smlnum, int maxit, QrQueue &q,
                                           int nacc, int &entry, int *iters) {
     const int lane = threadIdx.x & (LANES - 1);
+    const unsigned span = __builtin_amdgcn_readfirstlane(refl_span(hnorm));
     int i = m - 1, its = 0, total = 0, info = 0;
     while (i >= 0) {
         int l = 0;
@@ -653,7 +666,7 @@ __device__ __forceinline__ int qr_iterate(double *T, int ldt, int m, double hnor
             tr = a + d;
             det = a * d - b * c;
         }
-        qr_sweep<SETS>(T, ldt, m, l, i, tr, det, q, nacc, entry);
+        qr_sweep<SETS>(T, ldt, m, l, i, tr, det, span, q, nacc, entry);
     }
     *iters = total;
     return info;
