@@ -1134,6 +1134,43 @@ __device__ __forceinline__ void swap_begin(SwapState &w, const double *T, int ld
     __syncthreads();
 }
 
+// Whether the block at row r is a mover that goes up this round, and then its pair:
+// p rows above it, q of its own.
+__device__ __forceinline__ bool swap_pair(const SwapState &w, int r, int top, int &p, int &q) {
+    if (!w.mover[r]) return false;
+    p = w.head[r - 1] ? 1 : 2;
+    q = w.head[r + 1] ? 1 : 2;
+    return r - p >= top && !w.mover[r - p];
+}
+
+// The pairs of a round that has more than SWAP_PAIRS: the first ones from the top.
+// Which ones go first decides in which order their transforms meet in a row and a
+// column, so it must not be left to the order in which the waves come in: results are
+// the same bit for bit.  Waves 0..3 each go through the rows, wave t lists type t.
+__device__ __forceinline__ void swap_first_pairs(SwapState &w, int wave, int top, int kend) {
+    if (wave >= 4) return;
+    const int lane = threadIdx.x & (LANES - 1);
+    const unsigned long long below = (1ull << lane) - 1ull;
+    int total = 0, mine = 0;
+    for (int r0 = top + 1; r0 < kend && total < SWAP_PAIRS; r0 += LANES) {
+        const int r = r0 + lane;
+        int p = 1, q = 1;
+        const bool up = r < kend && swap_pair(w, r, top, p, q);
+        const unsigned long long all = __ballot(up);
+        const int slot = total + __popcll(all & below);
+        const bool take = up && (p - 1) * 2 + (q - 1) == wave && slot < SWAP_PAIRS;
+        const unsigned long long taken = __ballot(take);
+        if (take) {
+            w.st[slot] = r - p;
+            w.n[slot] = p + q;
+            w.list[wave][mine + __popcll(taken & below)] = slot;
+        }
+        total += __popcll(all);
+        mine += __popcll(taken);
+    }
+    if (lane == 0) w.cnt[wave] = mine;
+}
+
 // The transforms of one type's pairs, one per lane.
 template <int P, int Q>
 __device__ __forceinline__ void swap_transforms(SwapState &w, int type, double *T, int ld) {
@@ -1223,21 +1260,25 @@ __device__ __forceinline__ void swap_apply_all(SwapState &w, double *T, double *
 // NT threads call, after a barrier; ends with one.
 template <int NTH = NT>
 __device__ __forceinline__ int swap_round(SwapState &w, double *T, double *V, int ld, int nw, int top, int kend) {
+    static_assert(NTH >= 4 * LANES, "a wave per type of pair");
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / LANES);
     for (int r = top + 1 + (int)threadIdx.x; r < kend; r += NTH) {
-        if (!w.mover[r]) continue;
-        const int a = w.head[r - 1] ? r - 1 : r - 2;
-        if (a < top || w.mover[a]) continue;
+        int p, q;
+        if (!swap_pair(w, r, top, p, q)) continue;
         const int slot = atomicAdd(&w.total, 1);
         if (slot >= SWAP_PAIRS) continue;
-        const int p = r - a, q = w.head[r + 1] ? 1 : 2, type = (p - 1) * 2 + (q - 1);
-        w.st[slot] = a;
+        const int type = (p - 1) * 2 + (q - 1);
+        w.st[slot] = r - p;
         w.n[slot] = p + q;
         w.list[type][atomicAdd(&w.cnt[type], 1)] = slot;
     }
     __syncthreads();
-    const int pairs = min(w.total, SWAP_PAIRS);
+    const int found = w.total, pairs = min(found, SWAP_PAIRS);
     if (pairs == 0) return 0;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / LANES);
+    if (found > SWAP_PAIRS) {
+        swap_first_pairs(w, wave, top, kend);
+        __syncthreads();
+    }
     if (wave == 0) swap_transforms<1, 1>(w, 0, T, ld);
     else if (wave == 1) swap_transforms<1, 2>(w, 1, T, ld);
     else if (wave == 2) swap_transforms<2, 1>(w, 2, T, ld);
