@@ -150,7 +150,9 @@ extern "C" __global__ void __launch_bounds__(256) k_mlp_grad(const float *theta,
             gb1 += e1[r];
         }
         // weight gradients: sums over the tile's samples (k = sample); d1 is this
-        // wave's own (columns 16 w..), so no barrier is needed before it is read
+        // wave's own (columns 16 w..), so no barrier is needed before it is read, only
+        // the order of its lanes' stores and loads
+        wave_fence();
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
             const int s = 4 * t + lg;
