@@ -342,6 +342,10 @@ int neig_reorder(int n, double *S, int lds, double *Z, int ldz, const int *selec
 int neig_set_params(const neig_params *p);
 int neig_get_params(neig_params *p);
 
+/* The share that nibble 0 stands for in an active block of m rows, in neig_schur
+ * (batched 0) and in the batched solver (batched 1).  Needs no GPU. */
+int neig_default_nibble(int m, int batched);
+
 /* Counters of the most recent neig_schur call. */
 int neig_get_stats(neig_stats *s);
 

@@ -432,10 +432,7 @@ __device__ __forceinline__ int solve_one(const BProb &P, const BTune &tu, const 
         ndefl = (nd > 0) ? 0 : ndefl + 1;
         const int m2 = kbot - ktop + 1;
         if (m2 <= nmin) continue;
-        // 0: by the order of the block, as a sweep's cost grows with it and an AED's does
-        // not (measured on MI355X at 14 / 20 / 45 percent: 256 problems of order 32 to 300
-        // 28.0 / 27.1 / 25.4 ms, 512 of order 32 to 1024 233 / 231 / 248 ms)
-        const int nibble = A.nibble > 0 ? A.nibble : (m2 <= 256 ? 45 : 20);
+        const int nibble = A.nibble > 0 ? A.nibble : nibble_batched(m2);
         if (nd > 0 && 100 * nd > nibble * nw) continue;
         // shifts
         int ns = tu.ns;

@@ -949,16 +949,10 @@ class Solver {
         return out;
     }
 
+    int nibble_for(int m) const { return p_.nibble > 0 ? p_.nibble : nibble_single(m); }
+
     // Defaults measured on MI355X for random Hessenberg input: the AED window QR is a
     // latency-bound chain on one CU, so moderate windows deflate the most per unit time.
-    // The share of its window (percent) an AED must deflate for another AED to follow
-    // at once, for an active block of m rows.  A sweep's cost grows with m, an AED's
-    // does not, so small blocks sweep more readily.  Measured on MI355X (ms, at 14 / 20 /
-    // 33 / 45 percent): dense n = 512 65.2 / 65.3 / 52.9 / 46.0, random n = 512 21.8 /
-    // 22.6 / 21.6 / 21.8; dense n = 1500 216 / 205 / 191 / 173, random n = 1500 63.6 / 63.7
-    // / 73.9 / 77.6; random n = 5900 241 / 263 / 429 / 554.
-    int nibble_for(int m) const { return p_.nibble > 0 ? p_.nibble : (m <= 512 ? 45 : m <= 3000 ? 20 : 14); }
-
     int default_ns(int m) const {
         int ns = p_.ns > 0 ? p_.ns : (m < 300 ? 16 : 32);
         ns = std::min(ns, std::max(2, m / 3));
@@ -2060,6 +2054,8 @@ extern "C" int neig_get_params(neig_params *p) {
     *p = g_params;
     return 0;
 }
+
+extern "C" int neig_default_nibble(int m, int batched) { return batched ? nibble_batched(m) : nibble_single(m); }
 
 extern "C" int neig_get_stats(neig_stats *s) {
     if (!s) return -1;

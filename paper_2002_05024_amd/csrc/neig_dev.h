@@ -21,6 +21,28 @@ typedef double neig_d4 __attribute__((ext_vector_type(4)));
 #define NEIG_CHASE_MAX 96   // rows/cols of U in one chase window
 #define NEIG_MAX_CHAINS 32
 
+// nibble 0: the share of its window (percent) that an AED must deflate for another AED
+// to follow at once, for an active block of m rows.  A sweep's cost grows with m, an
+// AED's does not, so small blocks sweep more readily.  A dense matrix's form, whose
+// windows deflate little, would do so at any order; a random matrix loses by it from
+// some order on: by 45 and 33 percent above 512 rows, by 20 percent above 3000.  (About
+// there it is not sharp: the whole reduction of one random matrix took 3% less with 20
+// than with 14 at order 2500, 7% more at 3000, 6% more at 4000, and 1% less to 2% more
+// at 2600 and 2800; every dense one 2 to 5% less.)  Measured on MI355X, ms at 14 / 20 /
+// 33 / 45 percent:
+//   order   512: dense 65.2 / 65.3 / 52.9 / 46.0, random 21.8 / 22.6 / 21.6 / 21.8
+//   order   513: dense 63.9 / 59.5 / 52.9,        random 23.6 / 22.9 / 26.4
+//   order  1500: dense 218 / 209 / 190 / 173,     random 64.0 / 60.8 / 69.0 / 77.6
+//   order  2500: dense 412 / 401 / 372,           random 107.5 / 104.5 / 116.1
+//   order  3000: dense 520 / 505 / 492,           random 113.8 / 121.9 / 149.5
+//   order  4000: dense 788 / 772 / 744,           random 170.8 / 180.7 / 224.4
+__host__ __device__ inline int nibble_single(int m) { return m <= 512 ? 45 : m <= 3000 ? 20 : 14; }
+
+// The same in the batched solver, where one workgroup does both (ms at 14 / 20 / 45
+// percent: 256 problems of order 32 to 300 28.0 / 27.1 / 25.4, 512 of order 32 to 1024
+// 233 / 231 / 248).
+__host__ __device__ inline int nibble_batched(int m) { return m <= 256 ? 45 : 20; }
+
 // Reflector P = I - tau v v^T with v = (1, v1, v2) mapping x = (x0, x1, x2) to (beta, 0, 0).
 struct Refl {
     double tau, v1, v2, beta;
