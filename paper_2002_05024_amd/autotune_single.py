@@ -41,9 +41,9 @@ GRID = {
     "nw": [48, 64, 80, 96, 128, 192],
     "chain": [4, 6, 8],
     "chase_w": [64, 80, 96],
-    "nibble": [4, 8, 14, 25],
+    "nibble": [0, 4, 8, 14, 25],
 }
-DEFAULT = {"ns": 32, "nw": 64, "chain": 8, "chase_w": 96, "nibble": 14}
+DEFAULT = {"ns": 32, "nw": 64, "chain": 8, "chase_w": 96, "nibble": 0}  # the library's own (nibble by order)
 KEYS = tuple(DEFAULT)
 
 

@@ -1,11 +1,12 @@
 """What nibble 0 stands for on either side of the rule's edges, in the single-matrix and
-in the batched solver (both call the function asked here).  No GPU needed."""
+in the batched solver (both call the function asked here), and that the tuner starts
+from it.  No GPU needed."""
 import ctypes
 import os
 
 import pytest
 
-from paper_2002_05024_amd import binding
+from paper_2002_05024_amd import autotune_single, binding
 
 pytestmark = pytest.mark.skipif(not os.path.exists(binding.library_path()), reason="libneig.so not built")
 
@@ -16,3 +17,9 @@ def test_share_by_order(m, single, batched):
     lib = ctypes.CDLL(binding.library_path())
     assert lib.neig_default_nibble(m, 0) == single
     assert lib.neig_default_nibble(m, 1) == batched
+
+
+def test_tuner_starts_from_the_default():
+    for key, v in autotune_single.DEFAULT.items():
+        assert v in autotune_single.GRID[key]
+    assert autotune_single.DEFAULT["nibble"] == 0
