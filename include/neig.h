@@ -81,7 +81,8 @@ typedef struct neig_params {
                       next step's windows cover, applied on the call's stream, and the
                       rest, applied on a second stream beside the next chase launch
                       (Section 3.2: updates run concurrently with the chase);
-                      0: for orders of at least 8192; 1: always; 2: never               */
+                      0: for orders of at least 8192, while a step's updates are not much
+                      longer than its chase launch; 1: always; 2: never                 */
 } neig_params;
 
 /* Largest AED window.  Windows of at most 96 rows are solved in one workgroup's

@@ -85,7 +85,18 @@ constexpr int kStatusInts = 64;
 constexpr size_t kBatchedLds = (size_t)(NEIG_CHASE_MAX + 1) * (NEIG_CHASE_MAX + 2) * sizeof(double) +
                                (size_t)NEIG_CHASE_MAX * (NEIG_CHASE_MAX + 1) * sizeof(double);
 constexpr int kChainParamMax = 32;   // largest value of the parameter chain (chains have at most CHASE_MAX_BULGES)
-constexpr int kOverlapMinN = 8192;  // automatic overlap of sweep updates from this order on
+// Automatic overlap of a sweep's far updates with its chase launches: from this order
+// on (below, the extra launches and events cost more than the overlap hides), and while
+// the updates of a step, which take about 12 ps times order x chains x window, are not
+// much longer than the launch that they run beside, 0.95 us per chase step: then the
+// split only adds to what bounds the sweep, and the chase workgroups take whole compute
+// units from it.  Measured on MI355X, ms a sweep overlapped / not: windows of 64 and 4
+// chains at order 8192 13.6 / 14.9, 12000 24.0 / 24.9, 16000 35.2 / 36.9, 20000 50.9 /
+// 50.3, 28000 89.1 / 83.5; windows of 96 and 4 chains at 20000 48.4 / 52.5, 28000 88.8 /
+// 87.8; 8 chains, windows of 64 at 8192 18.4 / 19.1, 12000 34.1 / 33.4, 20000 79.2 /
+// 74.2, and of 96 at 8192 17.9 / 20.5, 16000 58.0 / 55.4.
+constexpr int kOverlapMinN = 8192;
+constexpr double kOverlapWork = 1.2e5;  // most order x chains x window per chase step
 
 template <class T>
 void grow(T **p, size_t *cap, size_t need) {
@@ -798,7 +809,8 @@ class Solver {
         // window's columns that start at or before hi in its near part, and a
         // right strip is split only if its window's columns start at or before
         // hi.
-        const bool ovl = p_.overlap == 1 || (p_.overlap == 0 && n_ >= kOverlapMinN);
+        const bool ovl = p_.overlap == 1 || (p_.overlap == 0 && n_ >= kOverlapMinN &&
+                                             (double)n_ * nchain * wmax <= kOverlapWork * (wmax - 3 * nbc));
         if (ovl) {
             ck(hipEventRecord(ws_.ev_join, st_));
             ck(hipStreamWaitEvent(ws_.ust, ws_.ev_join, 0));
