@@ -149,8 +149,8 @@ struct DeviceWs {
     float *pol_out = nullptr;
     float *h_pol_out = nullptr;
     float *mlp_part = nullptr; size_t mlp_part_cap = 0;
-    // Hessenberg reduction: V, Y, T, partials (one block, carved per call) and
-    // the column state with its two workgroup counters (zero between launches)
+    // Hessenberg reduction: V, Y, T, partials (one block, carved per call) and the
+    // column state (max |A| and the newest column's subdiagonal entry)
     double *hrd = nullptr; size_t hrd_cap = 0;
     // reordering: window descriptors and statuses of one round
     ReorderWin *rwin = nullptr; size_t rwin_cap = 0;

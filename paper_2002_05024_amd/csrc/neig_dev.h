@@ -1,8 +1,8 @@
 // neig_dev.h -- device-side building blocks shared by the libneig kernels (gfx950).
 //
-// Householder reflectors of length <= 3 (the bulge reflectors of Section 3.2),
-// the 2x2 standardisation of a real Schur block (Section 2, eq. 4), the
-// negligible-subdiagonal test, and wavefront reductions.  Everything is FP64.
+// The 2x2 standardisation of a real Schur block (Section 2, eq. 4), the
+// negligible-subdiagonal test, the rule of nibble 0, and wavefront reductions.
+// Everything is FP64.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -25,11 +25,11 @@ typedef double neig_d4 __attribute__((ext_vector_type(4)));
 // to follow at once, for an active block of m rows.  A sweep's cost grows with m, an
 // AED's does not, so small blocks sweep more readily.  A dense matrix's form, whose
 // windows deflate little, would do so at any order; a random matrix loses by it from
-// some order on: by 45 and 33 percent above 512 rows, by 20 percent above 3000.  (About
-// there it is not sharp: the whole reduction of one random matrix took 3% less with 20
-// than with 14 at order 2500, 7% more at 3000, 6% more at 4000, and 1% less to 2% more
-// at 2600 and 2800; every dense one 2 to 5% less.)  Measured on MI355X, ms at 14 / 20 /
-// 33 / 45 percent:
+// some order on: by 33 percent and more above 512 rows, by 20 percent above 3000.
+// (The second line is not sharp: with 20 instead of 14 the whole reduction of one random
+// matrix took 3% less at orders 2500 and 2600, 2% more at 2800, 7% more at 3000, 6% more
+// at 4000, and that of a dense one 1 to 7% less at every order.)  Measured on MI355X,
+// ms at 14 / 20 / 33 / 45 percent:
 //   order   512: dense 65.2 / 65.3 / 52.9 / 46.0, random 21.8 / 22.6 / 21.6 / 21.8
 //   order   513: dense 63.9 / 59.5 / 52.9,        random 23.6 / 22.9 / 26.4
 //   order  1500: dense 218 / 209 / 190 / 173,     random 64.0 / 60.8 / 69.0 / 77.6
@@ -42,73 +42,6 @@ __host__ __device__ inline int nibble_single(int m) { return m <= 512 ? 45 : m <
 // percent: 256 problems of order 32 to 300 28.0 / 27.1 / 25.4, 512 of order 32 to 1024
 // 233 / 231 / 248).
 __host__ __device__ inline int nibble_batched(int m) { return m <= 256 ? 45 : 20; }
-
-// Reflector P = I - tau v v^T with v = (1, v1, v2) mapping x = (x0, x1, x2) to (beta, 0, 0).
-struct Refl {
-    double tau, v1, v2, beta;
-};
-
-// Square root and reciprocal of an argument well inside the normal range
-// (1e-300 .. 1e300): the hardware approximations refined by Newton steps
-// (Goldschmidt's coupled iteration for the square root), correct to about one
-// unit in the last place.  They skip the range scaling that the general library
-// routines add, which sits on the critical path of every bulge step.
-__device__ __forceinline__ double sqrt_normal(double a) {
-    const double y = __builtin_amdgcn_rsq(a);
-    double g = a * y, h = 0.5 * y;
-    const double r = fma(-g, h, 0.5);
-    g = fma(g, r, g);
-    h = fma(h, r, h);
-    double d = fma(-g, g, a);
-    g = fma(d, h, g);
-    d = fma(-g, g, a);
-    return fma(d, h, g);
-}
-
-// The hardware reciprocal is good to about 2^-24 relative; each Newton step
-// squares the error, so two give the reciprocal to within about half a unit in
-// the last place (measured on gfx950 over 2^20 arguments spread over 2^+-40).
-__device__ __forceinline__ double rcp_normal(double a) {
-    double y = __builtin_amdgcn_rcp(a);
-    double e = fma(-a, y, 1.0);
-    y = fma(y, e, y);
-    e = fma(-a, y, 1.0);
-    return fma(y, e, y);
-}
-
-__device__ __forceinline__ Refl make_refl(double x0, double x1, double x2) {
-    Refl r;
-    const double s = fabs(x1) + fabs(x2);
-    if (s == 0.0) {
-        r.tau = 0.0; r.v1 = 0.0; r.v2 = 0.0; r.beta = x0;
-        return r;
-    }
-    const double mx = fmax(fabs(x0), s);
-    if (mx > 1e-150 && mx < 1e150) {
-        // no overflow or harmful underflow in the squares or in beta (x0 - beta);
-        // one division gives both 1/beta and 1/(x0 - beta)
-        const double nrm = sqrt_normal(x0 * x0 + x1 * x1 + x2 * x2);
-        const double beta = (x0 >= 0.0) ? -nrm : nrm;
-        const double d = x0 - beta;
-        const double q = rcp_normal(beta * d);
-        const double inv = beta * q;  // 1 / (x0 - beta)
-        r.tau = -d * d * q;           // (beta - x0) / beta
-        r.v1 = x1 * inv;
-        r.v2 = x2 * inv;
-        r.beta = beta;
-        return r;
-    }
-    const double rs = 1.0 / mx;
-    const double a = x0 * rs, b = x1 * rs, c = x2 * rs;
-    const double nrm = mx * sqrt(a * a + b * b + c * c);
-    const double beta = (x0 >= 0.0) ? -nrm : nrm;
-    const double inv = 1.0 / (x0 - beta);
-    r.tau = (beta - x0) / beta;
-    r.v1 = x1 * inv;
-    r.v2 = x2 * inv;
-    r.beta = beta;
-    return r;
-}
 
 // Standardisation of one 2x2 block of a real Schur form (Section 2, eq. 4).
 // Result: a rotation G = [[cs -sn][sn cs]] and the block G^T B G, which is upper
