@@ -265,7 +265,7 @@ __global__ void __launch_bounds__(HRD_THREADS * RG) k_hrd_a(HrdArgs p) {
     const double beta = coef[0], tau = coef[1], scal = coef[2];
     const int ex = cexp[0], ez = cexp[1];
     if (t < HRD_NB)
-        us[t] = t < ip ? vs[t] + ldexp(scal * hrd_add_waves<NW>(red, t), -ex - lift) : 0.0;
+        us[t] = t < ip ? fma(scal, ldexp(hrd_add_waves<NW>(red, t), -ex - lift), vs[t]) : 0.0;
     __syncthreads();
     double yu = 0.0, yw = 0.0;
 #pragma unroll
