@@ -152,25 +152,31 @@ struct ReflU {
 
 // The generating vector of a reflector, its squared length a, and the power of two
 // that it was scaled by when a left the range (u and q then belong to the scaled
-// vector; P is the same).  A zero vector becomes (1, 0, 0): a sign change.
+// vector; P is the same).  A zero vector becomes (1, 0, 0): a sign change, and so does
+// (x0, 0, 0), as which the sweep of a block goes on when the product of its shifts has
+// overflowed: thousands of exact ones leave Q orthogonal.
 struct GenVec {
     double x0, x1, x2, a, sc;
 };
 
 // The range of a in which u stays as it is: (2^-664, 2^664), |u| in (2^-332, 2^333).
 // The products with the matrix's entries x are then at most |u| |x| and |x| / |u|, so
-// they stay finite while ||H||_F < 2^600 (similarity transforms keep the norm); above,
-// every vector is scaled, and u is of order 1 as v of I - tau v v^T is.
+// they stay finite while ||H||_F < 2^500 (similarity transforms keep the norm), and so
+// does the product of two shifts; above (span 0), every vector is scaled, and u is of
+// order 1 as v of I - tau v v^T is.
 #define REFL_SPAN 0x53000000u
 #define REFL_LOCAL 1u  // stands for the span of a window whose norm the host does not know
-__host__ __device__ inline unsigned refl_span(double hnorm) { return hnorm < 0x1p600 ? REFL_SPAN : 0u; }
+__host__ __device__ inline unsigned refl_span(double hnorm) { return hnorm < 0x1p500 ? REFL_SPAN : 0u; }
 
 __device__ __forceinline__ GenVec gen_vec(double x0, double x1, double x2, unsigned span) {
     GenVec g{x0, x1, x2, fma(x0, x0, fma(x1, x1, x2 * x2)), 1.0};
     // by the exponent of a; the same in every lane
     if (__builtin_expect(__ballot((unsigned)__double2hiint(g.a) - 0x16700000u < span) == 0ull, 0)) {
         const double mx = fmax(fabs(x0), fmax(fabs(x1), fabs(x2)));
-        if (mx > 0.0 && mx < INFINITY) {
+        if (x1 == 0.0 && x2 == 0.0 && mx < INFINITY) {
+            g.sc = fabs(x0);
+            g.x0 = copysign(1.0, x0);
+        } else if (mx > 0.0 && mx < INFINITY) {
             const int e = ilogb(mx);
             g.x0 = ldexp(x0, -e); g.x1 = ldexp(x1, -e); g.x2 = ldexp(x2, -e);
             g.sc = ldexp(1.0, e);

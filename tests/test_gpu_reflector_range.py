@@ -78,3 +78,16 @@ def test_whole_reduction(n, sign):
     Hd = to_dev(H)
     r = neig.schur(Hd)
     check(H, to_host(Hd), to_host(r.Z))
+
+
+@pytest.mark.parametrize("n", [40, 96])
+def test_shifts_out_of_range(n):
+    """Entries around 2^1005: the determinant of a shift pair overflows, and the block
+    does not converge.  It stays a similarity, however many sweeps were tried."""
+    H = np.ldexp(np.triu(np.random.default_rng(1000 * n).standard_normal((n, n)), -1), 1005)
+    Hd = to_dev(H)
+    r = neig.small_schur(Hd)
+    S, Z = to_host(Hd), to_host(r.Z)
+    down = np.ldexp(1.0, -1005)
+    assert backward_error(H * down, S * down, Z) <= 50 * n * EPS
+    assert orthogonality(Z) <= 50 * n * EPS
