@@ -44,7 +44,7 @@ static_assert(MLP_NPARAM == 6848, "parameter layout");
 // barriers, about 2 us; a launch's first tile also waits about 8 us for its code
 // and weights).  Measured on MI355X, 4096 samples: gradient 29.2 -> 12.5 us and
 // reduction 29.8 -> 4.7 us (threads summed over k in turn and wrote a partial
-// gradient per 32 samples before); a training step 61 -> 23 us.
+// gradient per 32 samples before); a training step 61 -> 24 us.
 #define MLP_P 80       // row pitch of the LDS tiles: four rows lie 16 banks apart
 #define MLP_GRID 256   // most workgroups (and partial gradients)
 

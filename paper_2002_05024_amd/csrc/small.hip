@@ -102,7 +102,7 @@ __device__ __forceinline__ void lds_standardise(double *T, int ldt, double *Q, i
 //
 // The orthogonal factor does not feed back into T: waves 1 and 2 apply the
 // reflectors to Q's rows, in batches of FB that wave 0 publishes through a queue
-// in LDS.  Measured on MI355X on random 64-row windows (36 steps a sweep): 24 300
+// in LDS.  Measured on MI355X on random 64-row windows (36 steps a sweep): 23 550
 // cycles a sweep, 45 900 when the entries passed through LDS and the other waves
 // updated the far part of T; the n = 20000 random reduction 1.61 -> 1.11 s, an
 // n = 40 block 1.03 -> 0.54 ms.
@@ -547,7 +547,7 @@ __device__ __forceinline__ void qr_sweep(double *T, int ldt, int m, int l, int i
     while (k < i - 2) {
         const int ke = min(i - 2, k0 + FB);
         // by three, so that the shifts cost no moves; the loop starts on a multiple of 8
-        // bytes (64-row windows: 23 430 cycles a sweep, 23 910 where the code before it
+        // bytes (64-row windows: 23 550 cycles a sweep, 1% more where the code before it
         // ended half way, as most of its instructions then straddle two such units)
         asm volatile(".p2align 6");
         while (k + 3 <= ke) {
